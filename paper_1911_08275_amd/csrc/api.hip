@@ -688,7 +688,8 @@ static int pick_waves(const LdsLayout &LY, size_t *lds, int most = 4) {
 }
 
 template <int MODE, int PREC, int W>
-static int launch_pairs_t(hipStream_t st, const PairParams &P, size_t lds, int nwaves) {
+static int launch_pairs_t(hipStream_t st, const PairParams &P, size_t lds, int nwaves,
+                          int *grid_out) {
   auto kern = k_pairs<MODE, PREC, W>;
   static thread_local size_t set_lds = 0;
   if (lds > 65536 && lds > set_lds) {
@@ -713,6 +714,7 @@ static int launch_pairs_t(hipStream_t st, const PairParams &P, size_t lds, int n
     occ_per_cu = n;
   }
   const int grid = num_cus() * occ_per_cu;
+  *grid_out = grid;
   (void)hipGetLastError();  // drop any stale error so the check below is about this launch
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * nwaves), lds, st, P);
   const hipError_t e = hipGetLastError();
@@ -722,22 +724,33 @@ static int launch_pairs_t(hipStream_t st, const PairParams &P, size_t lds, int n
 }
 
 static int launch_pairs(hipStream_t st, int mode, int prec, int w, const PairParams &P,
-                        size_t lds, int nwaves) {
+                        size_t lds, int nwaves, int *grid) {
   if (mode == WPXI) {
     if (prec != F32R || w) return fail(CP_ERR_INTERNAL, "fused w_p + xi is binary32, unweighted");
-    return launch_pairs_t<WPXI, F32R, 0>(st, P, lds, nwaves);
+    return launch_pairs_t<WPXI, F32R, 0>(st, P, lds, nwaves, grid);
   }
   if (mode == XI) {
     if (prec == F32R)
-      return w ? launch_pairs_t<XI, F32R, 1>(st, P, lds, nwaves)
-               : launch_pairs_t<XI, F32R, 0>(st, P, lds, nwaves);
-    return w ? launch_pairs_t<XI, F64, 1>(st, P, lds, nwaves)
-             : launch_pairs_t<XI, F64, 0>(st, P, lds, nwaves);
+      return w ? launch_pairs_t<XI, F32R, 1>(st, P, lds, nwaves, grid)
+               : launch_pairs_t<XI, F32R, 0>(st, P, lds, nwaves, grid);
+    return w ? launch_pairs_t<XI, F64, 1>(st, P, lds, nwaves, grid)
+             : launch_pairs_t<XI, F64, 0>(st, P, lds, nwaves, grid);
   }
-  if (prec == F32R) return w ? launch_pairs_t<WP, F32R, 1>(st, P, lds, nwaves)
-                             : launch_pairs_t<WP, F32R, 0>(st, P, lds, nwaves);
-  return w ? launch_pairs_t<WP, F64, 1>(st, P, lds, nwaves)
-           : launch_pairs_t<WP, F64, 0>(st, P, lds, nwaves);
+  if (prec == F32R) return w ? launch_pairs_t<WP, F32R, 1>(st, P, lds, nwaves, grid)
+                             : launch_pairs_t<WP, F32R, 0>(st, P, lds, nwaves, grid);
+  return w ? launch_pairs_t<WP, F64, 1>(st, P, lds, nwaves, grid)
+           : launch_pairs_t<WP, F64, 0>(st, P, lds, nwaves, grid);
+}
+
+// Whether every item of a finished launch was taken: through the queue heads,
+// or, when there are no more items than waves, one by each wave (ItemQueue).
+static bool drained(const unsigned long long *stats, int64_t nitems, int64_t waves) {
+  if (nitems <= waves) return true;
+  for (int k = 0; k < kQueues; k++) {
+    const int64_t len = nitems * (k + 1) / kQueues - nitems * k / kQueues;
+    if (stats[5 + (size_t)k * kQStride] < (unsigned long long)len) return false;
+  }
+  return true;
 }
 
 // Binning setup shared by single calls and plans.
@@ -1360,7 +1373,8 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg) {
   size_t lds = 0;
   const int nwaves = pick_waves(LY, &lds, waves_most);
   if (!nwaves) return fail(CP_ERR_INVALID_ARG, "too many bins for the LDS budget");
-  if ((rc = launch_pairs(st, c.mode, prec, weighted, P, lds, nwaves))) return rc;
+  int grid = 0;
+  if ((rc = launch_pairs(st, c.mode, prec, weighted, P, lds, nwaves, &grid))) return rc;
   if (!noalloc) HIPCHK(hipEventRecord(ev[2], st));
 
   // ---- results
@@ -1413,12 +1427,8 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg) {
   const int ntiles = (int)hst[4];
   rc = map_err_flags(eflag);
   if (!rc) {
-    const int64_t nitems = (int64_t)ntiles * P.nsplit;
-    for (int k = 0; k < kQueues; k++) {
-      const int64_t len = nitems * (k + 1) / kQueues - nitems * k / kQueues;
-      if (hst[5 + k * kQStride] < (unsigned long long)len)
-        rc = fail(CP_ERR_INTERNAL, "work queue not drained");
-    }
+    if (!drained(hst, (int64_t)ntiles * P.nsplit, (int64_t)grid * nwaves))
+      rc = fail(CP_ERR_INTERNAL, "work queue not drained");
   }
   if (rc) {
     // failed calls leave zero outputs (the raw sums were copied into them)
@@ -1662,6 +1672,7 @@ struct Batch {
   int waves_most = 4;      // launch settings from the caller or the tuner
   int wpc = 1;             // copies of the w_p wave histogram
   int chunk_pct = 100;
+  int grid = 0;            // workgroups of the pair launch
   double pimax = 0.0;
   PairParams P{};
 };
@@ -1922,7 +1933,7 @@ static int batch_enqueue(cp_plan &pl, Batch &b, hipStream_t st) {
   hipLaunchKernelGGL(k_tiles, dim3(tb), dim3(256), 0, st, b.d_geom, nm, b.S.cstart, b.d_maxspan,
                      b.d_col_prefix, b.S.colcnt, b.S.coloff, b.S.tiles, 1);
   return launch_pairs(st, (pl.fused && &b == &pl.wp) ? WPXI : b.mode, b.prec, 0, b.P, b.lds,
-                      b.nwaves);
+                      b.nwaves, &b.grid);
 }
 
 // Enqueue one evaluation.  With timing events (eager mode only) the xi and
@@ -2228,12 +2239,8 @@ int cp_plan_results(cp_plan *pl, uint64_t *xi_npairs, uint64_t *wp_npairs) {
       std::vector<unsigned long long> st(kStatWords);
       HIPCHK(hipMemcpy(st.data(), b.d_stats, sizeof(unsigned long long) * kStatWords,
                        hipMemcpyDeviceToHost));
-      const int64_t nitems = (int64_t)st[4] * b.P.nsplit;
-      for (int k = 0; k < kQueues; k++) {
-        const int64_t len = nitems * (k + 1) / kQueues - nitems * k / kQueues;
-        if (st[5 + (size_t)k * kQStride] < (unsigned long long)len)
-          return fail(CP_ERR_INTERNAL, "work queue not drained");
-      }
+      if (!drained(st.data(), (int64_t)st[4] * b.P.nsplit, (int64_t)b.grid * b.nwaves))
+        return fail(CP_ERR_INTERNAL, "work queue not drained");
     }
     if (!out) continue;
     std::vector<unsigned long long> h((size_t)b.nout * pl->nmock);

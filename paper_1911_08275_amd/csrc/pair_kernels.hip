@@ -1160,6 +1160,56 @@ __device__ inline void loop_f64(const PairParams &P, WaveArea A, const LanePt &L
 
 // ------------------------------------------------------------------ kernel
 
+// A wave's walk through the work queues.  The nitems items are split into
+// kQueues contiguous ranges; a wave takes items of its workgroup's own queue
+// (home) first, then of the others.  qdrained: LDS mask of the queues that a
+// wave of this workgroup found drained; queues only drain, so the other waves
+// skip those without another device-scope atomic: at the end of a launch every
+// wave otherwise tried all eight heads, and those atomics queued at the memory
+// side with other waves' misses behind them.
+//
+// A launch with no more items than waves makes no atomic at all, the w-th wave
+// takes the w-th item: an atomic on a head that other XCDs use too takes about
+// 64 ns of its word's time, and with one per item and a failing one per
+// workgroup and queue a launch of 1 105 items took 86 us (38 with fixed items).
+// Above that the heads balance the load, which fixed first items did not
+// improve (xi at R_max 80: 6.9 and 7.1 ms).
+struct ItemQueue {
+  int victim = 0;   // queues left behind, counted from the home queue
+  bool first = true;
+
+  // The wave's next item, -1 when there is none.
+  __device__ inline int64_t next(unsigned long long *heads, int64_t nitems, uint32_t *qdrained,
+                                 int lane) {
+    if (nitems <= (int64_t)gridDim.x * (blockDim.x >> 6)) {
+      const int64_t w = uni64((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+      const bool f = first;
+      first = false;
+      return f && w < nitems ? w : -1;
+    }
+    const int home = (int)(blockIdx.x % kQueues);
+    int64_t tix = -1;
+    if (lane == 0) {
+      while (victim < kQueues) {
+        const int k = (home + victim) % kQueues;
+        const int64_t qb = nitems * k / kQueues, qe = nitems * (k + 1) / kQueues;
+        if ((*(volatile uint32_t *)qdrained >> k) & 1u) {
+          victim++;
+          continue;
+        }
+        const int64_t i = (int64_t)atomicAdd(&heads[k * kQStride], 1ull);
+        if (qb + i < qe) {
+          tix = qb + i;
+          break;
+        }
+        atomicOr(qdrained, 1u << k);
+        victim++;
+      }
+    }
+    return uni64(__shfl(tix, 0));
+  }
+};
+
 // Waves per SIMD the register allocation aims at: five (96 VGPRs) for most
 // instances; weighted xi with the binary32 filter holds a pair list per wave
 // and fits four workgroups per CU in LDS, so it takes the 128 VGPRs of four.
@@ -1171,12 +1221,7 @@ template <int MODE, int PREC, int W>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PairOcc<MODE, PREC, W>::waves)))
 void k_pairs(PairParams P) {
   extern __shared__ __align__(16) unsigned char smem[];
-  // bit k: a wave of this workgroup found queue k drained.  Queues only
-  // drain, so the other waves skip it without another device-scope atomic:
-  // at the end of a launch every wave otherwise tried all eight heads, and
-  // those atomics queued at the memory side with other waves' misses behind
-  // them.
-  __shared__ uint32_t qdrained;
+  __shared__ uint32_t qdrained;   // see ItemQueue
   if (threadIdx.x == 0) qdrained = 0u;
   const int lane = threadIdx.x & 63;
   const int wid = threadIdx.x >> 6;
@@ -1224,32 +1269,13 @@ void k_pairs(PairParams P) {
   const int64_t nitems = ntiles * nsplit;
   if (blockIdx.x == 0 && threadIdx.x == 0) P.stats[4] = (unsigned long long)ntiles;
   unsigned long long *heads = P.stats + 5;
-  const int home = (int)(blockIdx.x % kQueues);
-  int victim = 0;   // queues found empty so far, counted from the home queue
+  ItemQueue Q;
   int cur_mock = -1;
   unsigned long long since_flush = 0;
   const unsigned long long flush_limit = MODE == XI ? (1ull << 30) : (1ull << 24);
 
   for (;;) {
-    int64_t tix = -1;
-    if (lane == 0) {
-      while (victim < kQueues) {
-        const int k = (home + victim) % kQueues;
-        const int64_t qb = nitems * k / kQueues, qe = nitems * (k + 1) / kQueues;
-        if ((*(volatile uint32_t *)&qdrained >> k) & 1u) {
-          victim++;
-          continue;
-        }
-        const int64_t i = (int64_t)atomicAdd(&heads[k * kQStride], 1ull);
-        if (qb + i < qe) {
-          tix = qb + i;
-          break;
-        }
-        atomicOr(&qdrained, 1u << k);
-        victim++;
-      }
-    }
-    tix = uni64(__shfl(tix, 0));
+    const int64_t tix = Q.next(heads, nitems, &qdrained, lane);
     if (tix < 0) break;
     // item = (tile, chunk of its neighbour columns): consecutive items share
     // a tile, so its chunks run on different waves at the same time
