@@ -43,7 +43,6 @@ namespace cp {
 
 typedef const __attribute__((address_space(4))) float sfloat;
 typedef const __attribute__((address_space(4))) double sdouble;
-typedef const __attribute__((address_space(4))) int sint;
 
 __device__ inline double wave_min(double v) {
   for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
@@ -454,35 +453,31 @@ __device__ inline void stream_w(const float4 *fbase, const double4 *dbase, int j
 }
 
 // Narrows the records [jb, je) of a z-sorted cell to those with
-// zlo <= z <= zhi: two lane-parallel searches, 64 records per step, the
-// first from the front for the lower end, the second from the back for the
-// upper end.  jb, je and the result are wave-uniform.
-__device__ inline void zwindow(const double4 *pos, float zlo, float zhi, int lane, int &jb,
-                               int &je) {
+// zlo <= z <= zhi, each lane for a cell of its own: the two binary searches
+// step together, so a round of candidate cells pays one load latency per
+// halving of its longest cell (quarters, with three loads a step, took the same
+// time).  Done unit by unit instead, with the wave's lanes over one cell's
+// records, every unit paid two dependent load latencies and a scalar one for
+// its cell's range: pair kernel of 10^6 points, xi 0.84 against 0.80 ms, at
+// R_max 80 6.8 against 6.2, w_p 1.67 against 1.63.
+__device__ inline void zwindow(const double4 *pos, double zlo, double zhi, int &jb, int &je) {
   const double *zp = (const double *)pos + 2;   // z of record j at zp[4 j]
-  const double lo = (double)zlo, hi = (double)zhi;
-  int b = je;
-  for (int j0 = jb; j0 < je; j0 += 64) {
-    const int j = j0 + lane;
-    const bool ge = j < je && zp[4 * j] >= lo;
-    const unsigned long long m = __builtin_amdgcn_ballot_w64(ge);
-    if (m) {
-      b = j0 + __builtin_ctzll(m);
-      break;
+  int l0 = jb, r0 = je, l1 = jb, r1 = je;
+  const int last = je - 1;
+  while (l0 < r0 || l1 < r1) {
+    const int m0 = (l0 + r0) >> 1, m1 = (l1 + r1) >> 1;
+    const double z0 = zp[4 * (int64_t)min(m0, last)], z1 = zp[4 * (int64_t)min(m1, last)];
+    if (l0 < r0) {
+      if (z0 < zlo) l0 = m0 + 1;
+      else r0 = m0;
+    }
+    if (l1 < r1) {
+      if (z1 <= zhi) l1 = m1 + 1;
+      else r1 = m1;
     }
   }
-  int e = b;
-  for (int j1 = je; j1 > b; j1 -= 64) {
-    const int j = j1 - 64 + lane;
-    const bool le = j >= b && zp[4 * j] <= hi;
-    const unsigned long long m = __builtin_amdgcn_ballot_w64(le);
-    if (m) {
-      e = j1 - 64 + (63 - __builtin_clzll(m)) + 1;
-      break;
-    }
-  }
-  jb = b;
-  je = e;
+  jb = l0;
+  je = l1;
 }
 
 // Per-unit data handed to the inner loops.
@@ -1324,7 +1319,7 @@ void k_pairs(PairParams P) {
 
     for (int base = 0; base < total; base += 64) {
       const int t = base + lane;
-      int keep = 0, pruned = 0, cell = 0, packed = 0, slots = 0, win = 0, wzlo = 0, wzhi = 0;
+      int keep = 0, pruned = 0, cell = 0, packed = 0, slots = 0, rb = 0, re = 0;
       int mrg = 0;   // binary64: may join a run of z-cells (z-sorted, windows computable)
       if (t < total) {
         // column of the tile's list (order fixed by the host's split) and
@@ -1362,6 +1357,8 @@ void k_pairs(PairParams P) {
         if (ok) cell = (X * ny + Y) * nz + Z;
         if (ok) {
           const int b = P.cstart2[G2.sbase + cell], e = P.cstart2[G2.sbase + cell + 1];
+          rb = b;
+          re = e;
           if (e == b) {
             ok = false;
           } else {
@@ -1417,14 +1414,10 @@ void k_pairs(PairParams P) {
                                 : P.pimax * (1.0 + 1e-9);
                 hz = hz + 1e-9 * (fabs(blz) + fabs(bhz) + fabs(S2) + 1.0);
                 const double zl = blz - S2 - hz, zh = bhz - S2 + hz;
-                const bool cut = zl > B.lo[2] || zh < B.hi[2];
-                // (a run of cells takes the union of their windows, so each
-                // keeps its bounds)
-                if (cut || PREC == F64) {
-                  wzlo = __float_as_int(__double2float_rd(zl));
-                  wzhi = __float_as_int(__double2float_ru(zh));
+                if (zl > B.lo[2] || zh < B.hi[2]) {
+                  zwindow(P.pos2 + pbase2, zl, zh, rb, re);
+                  if (re <= rb) ok = false;
                 }
-                win = cut ? 1 : 0;
                 mrg = PREC == F64 && MODE != WPXI ? 1 : 0;
               }
             }
@@ -1432,8 +1425,8 @@ void k_pairs(PairParams P) {
         }
         if (ok) {
           // shift code per axis (-1, 0, +1 -> 0, 1, 2) in bits 1..6 of keep,
-          // z-window flag in bit 7, run flag in bit 8
-          keep = 1 | ((sx + 1) << 1) | ((sy + 1) << 3) | ((sz + 1) << 5) | (win << 7) | (mrg << 8);
+          // run flag in bit 8
+          keep = 1 | ((sx + 1) << 1) | ((sy + 1) << 3) | ((sz + 1) << 5) | (mrg << 8);
           packed = X | (Y << 10) | (Z << 20) | (own << 30);
         }
       }
@@ -1442,7 +1435,6 @@ void k_pairs(PairParams P) {
       while (mk) {
         const int src = __builtin_ctzll(mk);
         mk &= mk - 1;
-        const int c2 = __builtin_amdgcn_readlane(cell, src);
         const int pk = __builtin_amdgcn_readlane(packed, src);
         const int kc = __builtin_amdgcn_readlane(keep, src);
         const int sl = __builtin_amdgcn_readlane(slots, src);
@@ -1453,18 +1445,15 @@ void k_pairs(PairParams P) {
         // absolute positions, while the binary32 records are in each cell's
         // own frame, which a run would have to switch at every cell).  xi
         // joins cells of the same slot range, or any cells the general loop
-        // takes (own, or more than three slots); the run's z-window is the
-        // union of its cells' windows.
-        int nrun = 1, winr = kc & 128, slr = sl;
-        float wl = 0.f, wh = 0.f;
+        // takes (own, or more than three slots); the run reaches from its first
+        // cell's window to its last one's.
+        int nrun = 1, last = src, slr = sl;
         if (PREC == F64 && MODE != WPXI && (kc & 256)) {
           auto general = [&](int v, int p) {
             return ((p >> 30) & 1) || ((v >> 8) & 255) - (v & 255) > 2;
           };
           const bool gen = MODE == XI && general(sl, pk);
-          int last = src, pl = pk;
-          wl = __int_as_float(__builtin_amdgcn_readlane(wzlo, src));
-          wh = __int_as_float(__builtin_amdgcn_readlane(wzhi, src));
+          int pl = pk;
           while (last < 63 && ((mk >> (last + 1)) & 1ull)) {
             const int pk2 = __builtin_amdgcn_readlane(packed, last + 1);
             const int kc2 = __builtin_amdgcn_readlane(keep, last + 1);
@@ -1478,32 +1467,22 @@ void k_pairs(PairParams P) {
             mk &= ~(1ull << last);
             nrun++;
             pl = pk2;
-            winr |= kc2 & 128;
-            wl = fminf(wl, __int_as_float(__builtin_amdgcn_readlane(wzlo, last)));
-            wh = fmaxf(wh, __int_as_float(__builtin_amdgcn_readlane(wzhi, last)));
           }
         }
         const int X = pk & 1023, Y = (pk >> 10) & 1023, Z = (pk >> 20) & 1023;
         const bool own = (pk >> 30) & 1;
         const int sxx = ((kc >> 1) & 3) - 1, syy = ((kc >> 3) & 3) - 1, szz = ((kc >> 5) & 3) - 1;
         const bool shifted = (sxx | syy | szz) != 0;
-        sint *CS = (sint *)P.cstart2;
         Unit U;
         U.S[0] = sxx * box;
         U.S[1] = syy * box;
         U.S[2] = szz * box;
         U.strm = P.strm2 + pbase2;
         U.pos = P.pos2 + pbase2;
-        U.jb = CS[G2.sbase + c2];
-        U.je = CS[G2.sbase + c2 + nrun];
+        U.jb = __builtin_amdgcn_readlane(rb, src);
+        U.je = __builtin_amdgcn_readlane(re, last);
         U.slot_lo = slr & 255;
         U.slot_hi = (slr >> 8) & 255;
-        if (winr) {
-          const float zlo = nrun > 1 ? wl : __int_as_float(__builtin_amdgcn_readlane(wzlo, src));
-          const float zhi = nrun > 1 ? wh : __int_as_float(__builtin_amdgcn_readlane(wzhi, src));
-          zwindow(U.pos, zlo, zhi, lane, U.jb, U.je);
-          if (U.je <= U.jb) continue;
-        }
         const unsigned long long nj = (unsigned long long)(U.je - U.jb);
         st_cells += (unsigned long long)nrun;
         since_flush += nj;
