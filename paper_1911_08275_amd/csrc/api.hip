@@ -213,6 +213,36 @@ static bool build_table(const EdgeF &C, const EdgeF &Av, int shift, Table &T) {
   return true;
 }
 
+// Few-edge table over the cells of a decision table T (same index): entry =
+// (edge, slot above it | 1 << 31), see wp_record in pair_kernels.hip.  An edge
+// belongs to every cell that holds a value within eps of it; a cell near two
+// edges is marked, a cell near none has the edge -3e38.
+static void build_few(const EdgeD &E, double eps, const Table &T, int shift, Table &F) {
+  F.lo = T.lo;
+  F.hi = T.hi;
+  F.e.assign(T.hi - T.lo + 1, make_uint2(0, 0));
+  const double w = eps * (1.0 + 1e-6) + 1e-37;
+  for (int m = T.lo; m <= T.hi; m++) {
+    const double lo = m == T.lo ? -INFINITY : (double)bitsf((uint32_t)m << shift);
+    const double hi = m == T.hi ? INFINITY : (double)bitsf((uint32_t)(m + 1) << shift);
+    int near = 0, last = 0, below = 0;
+    for (int k = 0; k < E.size(); k++) {
+      // (s >= 0 = E_0 always)
+      if (E[k] == 0.0) { below++; continue; }
+      if (E[k] + w >= lo && E[k] - w <= hi) {
+        near++;
+        last = k;
+      } else if (E[k] < lo) {
+        below++;
+      }
+    }
+    uint2 e;
+    if (near == 1) e = make_uint2(fbits((float)E[last]), (uint32_t)(last + 1));
+    else e = make_uint2(fbits(kNegBig), (uint32_t)below | (near ? 0x80000000u : 0u));
+    F.e[m - T.lo] = e;
+  }
+}
+
 // ---------------------------------------------------------------- geometry
 
 struct Geometry {
@@ -757,7 +787,7 @@ static bool drained(const unsigned long long *stats, int64_t nitems, int64_t wav
 struct Binning {
   EdgeD E;
   EdgeF C32, A32;
-  Table t32, t64;
+  Table t32, t64, few;   // few: few-edge table over t32's cells (w_p, binary32)
   int shift;
   float AB32;
   float eps32, eps32_3;
@@ -804,6 +834,7 @@ static int make_binning(int mode, int prec, const double *edges, int nedges, dou
   B.eps32_3 = f32_up(B.bnd.eps + 2.0 * std::ldexp(1.0, -24) * EB * 1.01);
   B.C32 = C32;
   B.A32 = A32;
+  if (mode == WP && prec == F32R) build_few(B.E, B.eps32_3, B.t32, B.shift, B.few);
   B.dpi = mode == WP ? pimax / npi : 1.0;
   if (mode == WP) {
     const double u = std::ldexp(1.0, -24);
@@ -872,6 +903,10 @@ static bool make_binning_wpxi(const double *edges, int nedges, const Binning &Bw
   Bx.AB32 = A[nb];
   Bx.C32 = C;
   Bx.A32 = A;
+  // the few-edge differences are formed from the first r_p edge's: two more
+  // roundings of at most the larger E_B each
+  Bx.eps32_3 = f32_up(bound + 4.04 * u * std::max(EB, Bw.E[Bw.E.size() - 1]));
+  build_few(Bx.E, Bx.eps32_3, Bx.t32, Bx.shift, Bx.few);
   return true;
 }
 
@@ -1296,7 +1331,7 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg) {
       if (bytes) memcpy(hup + ((const char *)dev - up0), src, bytes);
     };
     put(d_sm, &hs, sizeof(hs));
-    put(d_t32, B.t32.e.data(), (size_t)n32 * 8);
+    put(d_t32, (few_edge_tables(c.mode, prec, weighted) ? B.few : B.t32).e.data(), (size_t)n32 * 8);
     put(d_t64, B.t64.e.data(), (size_t)n64 * 8);
     put(d_E, B.E.data(), (size_t)c.nedges * 8);
     put(d_c32, B.C32.data(), (size_t)c.nedges * 4);
@@ -1817,7 +1852,8 @@ static int batch_upload(cp_plan &pl, Batch &b) {
   HIPCHK(hipMemcpy(b.d_col_prefix, b.col_prefix.data(), 8 * (nm + 1), hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(b.d_maxspan, b.maxspan.data(), 4 * nm, hipMemcpyHostToDevice));
   if (!b.B.t32.e.empty())
-    HIPCHK(hipMemcpy(b.d_t32, b.B.t32.e.data(), 8 * b.B.t32.e.size(), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(b.d_t32, (few_edge_tables(b.mode, b.prec, 0) ? b.B.few : b.B.t32).e.data(),
+                     8 * b.B.t32.e.size(), hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(b.d_t64, b.B.t64.e.data(), 8 * b.B.t64.e.size(), hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(b.d_E, b.B.E.data(), 8 * (b.nb + 1), hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(b.d_c32, b.B.C32.data(), 4 * (b.nb + 1), hipMemcpyHostToDevice));
@@ -2141,7 +2177,7 @@ static int plan_create(const cp_points *mocks, int nmocks, const double *xi_edge
     }
     if (pl->fused) {
       const Binning &X = pl->xbin;
-      if (hipMemcpy(pl->d_tabx, X.t32.e.data(), 8 * X.t32.e.size(), hipMemcpyHostToDevice) !=
+      if (hipMemcpy(pl->d_tabx, X.few.e.data(), 8 * X.few.e.size(), hipMemcpyHostToDevice) !=
               hipSuccess ||
           hipMemcpy(pl->d_Ex, X.E.data(), 8 * (size_t)xi_nedges, hipMemcpyHostToDevice) !=
               hipSuccess) {
@@ -2157,6 +2193,7 @@ static int plan_create(const cp_points *mocks, int nmocks, const double *xi_edge
       P.Ex = pl->d_Ex;
       P.nbx = xi_nedges - 1;
       P.AB32x = X.AB32;
+      P.epsx32 = X.eps32_3;
       P.histx = pl->xi.d_hist;
       P.histx_stride = pl->xi.nout;
     }

@@ -146,7 +146,7 @@ struct PairParams {
   const int *cstart2;        // cell starts of set 2 (relative to pbase)
   const CellBox *cbox2;      // cell bounding boxes of set 2
   // binning
-  const uint2 *tab32;        // binary32 decision table (FP32 mode)
+  const uint2 *tab32;        // binary32 decision table (FP32 mode), or few-edge table
   const uint2 *tab64;        // decision table for fl32(s64) (FP64 values)
   int tab32_lo, tab32_hi, tab64_lo, tab64_hi;
   int tab_shift;
@@ -178,13 +178,14 @@ struct PairParams {
   unsigned long long *stats; // kStatWords: candidates, rechecks, cell pairs, pruned,
                              // tile count (written by the pair kernel), queue heads
   int hist_stride;           // nb * npi
-  // xi of a WPXI launch: decision table of s~ = fl32(pi~^2 + rp~^2) (bands
+  // xi of a WPXI launch: few-edge table of s~ = fl32(pi~^2 + rp~^2) (bands
   // of its own error bound), squared edges, histogram
   const uint2 *tabx;
   int tabx_lo, tabx_hi, tabx_shift;
   const double *Ex;          // nbx + 1
   int nbx;
   float AB32x;               // s~ >= AB32x -> certainly >= the last xi edge
+  float epsx32;              // bound on |(s~ - E) - (s - E)| of the few-edge loops' xi differences
   unsigned long long *histx; // [nmock][nbx]
   int histx_stride;
 };
@@ -224,6 +225,12 @@ struct LdsLayout {
 __host__ __device__ constexpr bool xi_f32_weighted(int mode, int prec, int weighted) {
   return mode == XI && prec == F32R && weighted;
 }
+// Kernels whose binary32 tables are few-edge tables (pair_kernels.hip,
+// wp_record) and which run no binary64 loop, hence hold no binary64 table: a
+// grid with a wrapped axis runs binary64 kernels.
+__host__ __device__ constexpr bool few_edge_tables(int mode, int prec, int weighted) {
+  return mode != XI && prec == F32R && !weighted;
+}
 // List entries per wave: fewer than 64 are left over after a drain, and a
 // group of four records adds at most 4 x 64.
 constexpr int kListCap = 64 + 4 * 64;
@@ -239,6 +246,7 @@ __host__ __device__ inline LdsLayout lds_layout(int mode, int prec, int weighted
   size_t off = 0;
   L.tab32 = off;
   if (xi_f32_weighted(mode, prec, weighted)) n32 = 0;
+  if (few_edge_tables(mode, prec, weighted)) n64 = 0;
   off += (size_t)(prec == F32R ? n32 : 0) * 8;
   L.tab64 = off;
   off += (size_t)n64 * 8;

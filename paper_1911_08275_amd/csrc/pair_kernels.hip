@@ -91,6 +91,14 @@ __device__ inline int exact_slot(const double *E, int nb, double s) {
   return k + 1;
 }
 
+// The same scanned from the outermost edge inwards, where most bounds of
+// separations lie.
+__device__ inline int exact_slot_top(const double *E, int nb, double s) {
+  int k = nb + 1;
+  while (k > 0 && s < E[k - 1]) k--;
+  return k;
+}
+
 // Pi bin of a binary64 |dz| < pi_max: l with q_l <= pi < q_{l+1},
 // q_l = fl(l * dpi).  The product with fl(1 / dpi) lands within one of l
 // (|dz| / dpi < 257 and both roundings are relative), so one compare each
@@ -209,39 +217,12 @@ struct WaveArea {
   uint32_t *list;   // weighted xi, binary32 mode: (tile lane, record) pairs to evaluate
 };
 
-// a * b + c on the low 24 bits of a and b, and (a << s) + c, one
-// instruction each (the compiler otherwise forms a multiply, a shift and a
-// three-way add).
-__device__ inline uint32_t mad_u24(uint32_t a, uint32_t b, uint32_t c) {
-  uint32_t r;
-  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
+// (a << s) + c in one instruction.
 __device__ inline uint32_t lshl_add(uint32_t a, uint32_t s, uint32_t c) {
   uint32_t r;
   asm("v_lshl_add_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(s), "v"(c));
   return r;
 }
-
-// Address of the (r_p, pi) counter of slot s and pi bin l in a wave's
-// histogram, word (s * npi + l) * wpc + base (wpc copies, interleaved; wpc a
-// power of two).  The table entry's low bits carry t = s + 1 - ch, where ch
-// says the value lies above the entry's upper threshold: the -1 is folded
-// into the lane's base address and ch picks the base one row up, so the
-// address is a select, a 24-bit multiply-add and a shift-add.
-struct WpIndex {
-  uint32_t row4, hb, hb1;
-  uint32_t lsh;
-  __device__ WpIndex(uint32_t *hist, int npi, int wpc, int base) {
-    row4 = (uint32_t)in_vgpr(npi * wpc * 4);
-    lsh = (uint32_t)in_vgpr(wpc == 2 ? 3 : (wpc == 4 ? 4 : (wpc == 8 ? 5 : 2)));
-    hb = lds_addr(hist) + 4u * (uint32_t)base - row4;
-    hb1 = hb + row4;
-  }
-  __device__ uint32_t *at(uint32_t t, bool ch, int l) const {
-    return lds_ptr(lshl_add((uint32_t)l, lsh, mad_u24(t, row4, ch ? hb1 : hb)));
-  }
-};
 
 // xi counters rows[s * 32 + c] of slots s = 0 .. nb + 1, one column per
 // lane pair (c = lane mod 32): lane s - 1 takes slot s's wave total, and one
@@ -663,105 +644,213 @@ __device__ inline void recheck_wp(const PairParams &P, WaveArea A, const LanePt 
                        exact_pibin(pz64, P.dpi, P.inv_dpi, P.npi)) * P.wpc + cpy], 1u);
 }
 
-// wp, unweighted: certain pairs are counted at once, uncertain ones
-// re-evaluated in binary64 on the spot (as in the general xi loop).
-template <bool OWN, bool SHIFT>
-__device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt &L, int lane,
-                                   float rx, float ry, float rz, float ra, const Unit &U,
-                                   const uint2 *tab32, const double *sE, uint32_t &nrechk) {
-  const int npi = in_vgpr(P.npi), wpc = in_vgpr(P.wpc), lo = in_vgpr(P.tab32_lo);
-  const int sh = in_vgpr(P.tab_shift);
-  const int base = lane & (wpc - 1);
-  const uint2 *tb = tab32 - P.tab32_lo;
-  const float AB = in_vgpr(P.AB32), phi = in_vgpr(P.pi_hi32);
-  const float inv = in_vgpr(P.inv_dpi32);
-  const float pd = in_vgpr(P.pi_delta), pd1 = in_vgpr(1.0f - P.pi_delta);
-  const WpIndex H(A.hist, npi, wpc, base);
-  uint32_t nunc = 0;
-  stream_f32(U.strm, U.jb, U.je, [&](int j, float qx, float qy, float qz, float qw) {
-    const float v = __builtin_fmaf(ry, qy, __builtin_fmaf(rx, qx, ra)) + qw;
-    const float pz = fabsf(qz - rz);
-    bool pre = (v < AB) && (pz < phi);
-    if (OWN) pre = pre && (j > L.iloc);
-    if (pre) {
-      const uint2 e = tb[max(__float_as_int(v) >> sh, lo)];
-      const float f = pz * inv;
-      const float fr = __builtin_amdgcn_fractf(f);   // f - floor(f), exact for f >= 0
-      const bool ch = v >= __uint_as_float(e.y);
-      const bool unc = (v >= __uint_as_float(e.x) && !ch) || fr < pd || fr > pd1;
-      if (unc) {
-        recheck_wp<SHIFT>(P, A, L, U, j, sE, base);
-        nunc++;
-      } else {
-        atomicAdd(H.at(e.y & 63u, ch, (int)f), 1u);
-      }
-    }
-  });
-  nrechk += nunc;
-}
+// Unweighted w_p, and w_p with xi in one pass (WPXI: s~ = fl32(pi~^2 + rp~^2)
+// from the same binary32 values), decide a pair by the signs of differences to
+// edges, without compares: on gfx950 subtractions, adds, shifts and logic of
+// two operands issue in two cycles a wave, compares, minima and everything with
+// three operands in four.  The edges come from the unit's slot range when it
+// spans few, or else from a table cell.
+//
+// Few-edge table (tab32, tabx of these modes): indexed by the estimate's bits
+// as the decision tables are, entry = (edge t, row): the cell's values can only
+// be about t, row is the byte offset of the counters above it (one row less
+// below), bit 31 marks a cell near two edges, whose pairs all count as
+// uncertain; a cell near none has t = -3e38.
 
-// w_p and xi in one pass (WPXI, unweighted): the w_p decisions of
-// loop_wp_f32, and for xi the estimate s~ = fl32(pi~^2 + rp~^2) from the same
-// binary32 values, decided through its own table (bands of the WPXI error
-// bound); an uncertain xi pair is re-evaluated in binary64.  Pairs are
-// counted once for each statistic they belong to.
-template <bool OWN>
-__device__ inline void loop_wpxi_f32(const PairParams &P, WaveArea A, const LanePt &L, int lane,
-                                     float rx, float ry, float rz, float ra, const Unit &U,
-                                     const uint2 *tab32, const double *sE, const uint2 *tabx,
-                                     const double *sEx, uint32_t &nrechk) {
-  const int npi = in_vgpr(P.npi), wpc = in_vgpr(P.wpc), lo = in_vgpr(P.tab32_lo);
-  const int sh = in_vgpr(P.tab_shift);
-  const int base = lane & (wpc - 1);
-  const uint2 *tb = tab32 - P.tab32_lo;
-  const float AB = in_vgpr(P.AB32), phi = in_vgpr(P.pi_hi32);
-  const float inv = in_vgpr(P.inv_dpi32);
-  const float pd = in_vgpr(P.pi_delta), pd1 = in_vgpr(1.0f - P.pi_delta);
-  const int lox = in_vgpr(P.tabx_lo), shx = in_vgpr(P.tabx_shift), nbx = P.nbx;
-  const uint2 *tbx = tabx - P.tabx_lo;
-  const float ABx = in_vgpr(P.AB32x);
-  const WpIndex H(A.hist, npi, wpc, base);
-  // xi counter of slot s at row s, column lane mod 32: byte address (s + 1) * 128 + hx
-  const uint32_t hx = lds_addr(A.histx) + 4u * (uint32_t)(lane & 31) - 128u, hx1 = hx + 128u;
-  uint32_t nunc = 0;
-  stream_f32(U.strm, U.jb, U.je, [&](int j, float qx, float qy, float qz, float qw) {
-    const float v = __builtin_fmaf(ry, qy, __builtin_fmaf(rx, qx, ra)) + qw;
-    const float pz = fabsf(qz - rz);
-    const bool ok = OWN ? (j > L.iloc) : true;
-    if (ok && v < AB && pz < phi) {
-      const uint2 e = tb[max(__float_as_int(v) >> sh, lo)];
-      const float f = pz * inv;
-      const float fr = __builtin_amdgcn_fractf(f);   // f - floor(f), exact for f >= 0
-      const bool ch = v >= __uint_as_float(e.y);
-      const bool unc = (v >= __uint_as_float(e.x) && !ch) || fr < pd || fr > pd1;
-      if (unc) {
-        recheck_wp<true>(P, A, L, U, j, sE, base);
-        nunc++;
-      } else {
-        atomicAdd(H.at(e.y & 63u, ch, (int)f), 1u);
-      }
+// One record in that way, pair by pair, for the few records that the loop
+// below finds to hold an uncertain pair: those are re-evaluated in binary64.
+template <bool XIDEC>
+__device__ inline void wp_record(const PairParams &P, WaveArea A, const LanePt &L, int jmin,
+                                 int lane, float rx, float ry, float rz, float ra, const Unit &U,
+                                 int j, const uint2 *tab32, const double *sE, const uint2 *tabx,
+                                 const double *sEx, uint32_t &nrechk) {
+  sfloat *q = (sfloat *)(U.strm + j);
+  const float v = __builtin_fmaf(ry, q[1], __builtin_fmaf(rx, q[0], ra)) + q[3];
+  const float pz = fabsf(q[2] - rz);
+  const int cpy = lane & (P.wpc - 1), row4 = P.npi * P.wpc * 4;
+  const bool ok = j > jmin;
+  if (ok && v < P.AB32 && pz < P.pi_hi32) {
+    const uint2 e = tab32[min(max(__float_as_int(v) >> P.tab_shift, P.tab32_lo), P.tab32_hi) - P.tab32_lo];
+    const float f = pz * P.inv_dpi32, d = v - __uint_as_float(e.x);
+    const float fr = __builtin_amdgcn_fractf(f);
+    if (fabsf(d) < P.eps32_3 || (int)e.y < 0 || fr < P.pi_delta || fr > 1.0f - P.pi_delta) {
+      recheck_wp<true>(P, A, L, U, j, sE, cpy);
+      nrechk++;
+    } else {
+      const int at = (int)e.y - (d < 0.f ? row4 : 0) + ((int)f * P.wpc + cpy) * 4;
+      atomicAdd(lds_ptr(lds_addr(A.hist) + (uint32_t)at), 1u);
     }
+  }
+  if (XIDEC) {
     const float sx = __builtin_fmaf(pz, pz, v);
-    if (ok && sx < ABx) {
-      const uint2 e = tbx[max(__float_as_int(sx) >> shx, lox)];
-      const bool ch = sx >= __uint_as_float(e.y);
-      uint32_t ad;
-      if (sx >= __uint_as_float(e.x) && !ch) {
-        // binary64 re-evaluation (the reference separation)
+    if (ok && sx < P.AB32x) {
+      const uint2 e = tabx[min(max(__float_as_int(sx) >> P.tabx_shift, P.tabx_lo), P.tabx_hi) - P.tabx_lo];
+      const float d = sx - __uint_as_float(e.x);
+      int at = (int)e.y - (d < 0.f ? 128 : 0);
+      if (fabsf(d) < P.epsx32 || (int)e.y < 0) {
         sdouble *DP = (sdouble *)U.pos;
         const int wz[3] = {0, 0, 0};
         double dx, dy, dz;
         ref_sep<true, false>(L.x, L.y, L.z, DP[4 * j], DP[4 * j + 1], DP[4 * j + 2], U.S, wz, 0.0,
                              0.0, dx, dy, dz);
-        ad = ((uint32_t)exact_slot(sEx, nbx, (dx * dx + dy * dy) + dz * dz) << 7) + hx1;
-        nunc++;
-      } else {
-        ad = lshl_add(e.y & 63u, 7u, ch ? hx1 : hx);
+        at = exact_slot(sEx, P.nbx, (dx * dx + dy * dy) + dz * dz) * 128;
+        nrechk++;
       }
-      atomicAdd(lds_ptr(ad), 1u);
+      atomicAdd(lds_ptr(lds_addr(A.histx) + (uint32_t)(at + (lane & 31) * 4)), 1u);
     }
-  });
-  nrechk += nunc;
+  }
+}
+
+// A unit's records.  K >= 1: every pair lands in one of the K + 1 r_p slots
+// slot_hi - K .. slot_hi; d_k = v~ - E_k with the first edge folded into the
+// lane's constant and the others one add apart (as in the three-slot xi loop).
+// K = 0: any slots, one edge per pair from the table.  KX >= 1: the pairs' xi
+// slots are xlo .. xlo + KX, counted by sign in registers; KX = 0: no xi here
+// (none in range, or counted at once); KX = -1 (with K = 0): xi table.  OWN:
+// pairs j > i only.  Four rows go together: the smallest |d_k| and the largest
+// distance of a pi fraction from 1/2 tell with one branch whether any of their
+// pairs is uncertain, and then the four take wp_record.  Bound: VALU issue.
+// Against a decision-table lookup per pair with its compares: w_p of 10^6
+// points 1.88 to 1.74 ms a call, 16 catalogues' w_p and xi 51.0 to 48.5 ms.
+// exec = valid lanes.
+template <int K, int KX, bool OWN>
+__device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt &L, int lane,
+                                   float rx, float ry, float rz, float ra, const Unit &U, int xlo,
+                                   const uint2 *tab32, const double *sE, const uint2 *tabx,
+                                   const double *sEx, uint32_t &nrechk) {
+  constexpr bool TAB = K == 0, XT = KX < 0;
+  constexpr int NK = K > 1 ? K : 1, NX = KX > 1 ? KX : 1;
+  const int wpc = P.wpc, k0 = U.slot_hi - K;   // edges k0 .. k0 + K - 1
+  const double E0 = TAB ? 0.0 : sE[k0];
+  const float b = TAB ? ra : (float)((double)ra - E0);
+  float c[NK], cx[NX];
+#pragma unroll
+  for (int k = 1; k < K; k++) c[k] = (float)(E0 - sE[k0 + k]);
+#pragma unroll
+  for (int k = 0; k < KX; k++) cx[k] = (float)(E0 - sEx[xlo + k]);
+  const float eps = in_vgpr(P.eps32_3), epsx = KX ? in_vgpr(P.epsx32) : 0.f;
+  const float hm = in_vgpr(0.5f - P.pi_delta), inv = in_vgpr(P.inv_dpi32);
+  const float phi = in_vgpr(P.pi_hi32);
+  // pairs at or beyond E_B are not counted: with K >= 1 that is the last edge,
+  // when slot_hi lies beyond the bins
+  const float top = TAB ? in_vgpr(P.AB32) : U.slot_hi > P.nb ? 0.f : 3.0e38f;
+  const float topx = XT ? in_vgpr(P.AB32x) : 0.f;
+  const uint32_t row4 = (uint32_t)(P.npi * wpc * 4);
+  const uint32_t nrow4 = (uint32_t)in_vgpr((int)(0u - row4));
+  const uint32_t lsh = (uint32_t)in_vgpr(wpc == 2 ? 3 : (wpc == 4 ? 4 : (wpc == 8 ? 5 : 2)));
+  const uint32_t h0 = lds_addr(A.hist) + 4u * (uint32_t)(lane & (wpc - 1));
+  const uint32_t hi = TAB ? h0 : h0 + (uint32_t)U.slot_hi * row4;
+  const int lo = in_vgpr(P.tab32_lo), top_ix = in_vgpr(P.tab32_hi), sh = in_vgpr(P.tab_shift);
+  const uint2 *tb = tab32 - P.tab32_lo;
+  const int lox = in_vgpr(P.tabx_lo), topx_ix = in_vgpr(P.tabx_hi), shx = in_vgpr(P.tabx_shift);
+  const uint2 *tbx = tabx - P.tabx_lo;
+  const uint32_t hx = XT ? lds_addr(A.histx) + 4u * (uint32_t)(lane & 31) : 0u;
+  const int jmin = OWN ? L.iloc : -1;
+  uint32_t nx[NX], skip = 0;
+#pragma unroll
+  for (int k = 0; k < NX; k++) nx[k] = 0;
+  // rows j .. j + n - 1 (n <= 4; the records past them are loaded but not used)
+  auto rows4 = [&](int j, const float *q, auto full, int n) {
+    constexpr bool FULL = decltype(full)::value;
+    float v[4], d[4], dz[4], f[4], s[4], mn = 3.0e38f, mx = 0.f, mnx = 3.0e38f;
+    uint32_t m[4], sx[NX], flag = 0;
+    uint2 e[4], ex[4];
+#pragma unroll
+    for (int k = 0; k < NX; k++) sx[k] = 0;
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      v[u] = __builtin_fmaf(ry, q[4 * u + 1], __builtin_fmaf(rx, q[4 * u], b)) + q[4 * u + 3];
+      if (TAB) e[u] = tb[min(max(__float_as_int(v[u]) >> sh, lo), top_ix)];
+      dz[u] = q[4 * u + 2] - rz;
+      f[u] = dz[u] * inv;
+      if (KX) s[u] = __builtin_fmaf(dz[u], dz[u], v[u]);
+      if (XT) ex[u] = tbx[min(max(__float_as_int(s[u]) >> shx, lox), topx_ix)];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const float d0 = TAB ? v[u] - __uint_as_float(e[u].x) : v[u];
+      d[u] = d0;
+      m[u] = __float_as_uint(d0) >> 31;
+      mn = fminf(mn, fabsf(d0));
+      if (TAB) flag |= e[u].y;
+#pragma unroll
+      for (int k = 1; k < K; k++) {
+        d[u] = d0 + c[k];   // ends as the last edge's
+        m[u] += __float_as_uint(d[u]) >> 31;
+        mn = fminf(mn, fabsf(d[u]));
+      }
+      mx = fmaxf(mx, fabsf(__builtin_amdgcn_fractf(fabsf(f[u])) - 0.5f));
+#pragma unroll
+      for (int k = 0; k < KX; k++) {
+        const float dk = s[u] + cx[k];
+        const uint32_t g = __float_as_uint(dk) >> 31;
+        sx[k] += FULL || u < n ? g : 0u;
+        mnx = fminf(mnx, fabsf(dk));
+      }
+      if (XT) {
+        const float dk = s[u] - __uint_as_float(ex[u].x);
+        mnx = fminf(mnx, fabsf(dk));
+        flag |= ex[u].y;
+        ex[u].x = __float_as_uint(dk) >> 31;
+      }
+    }
+    bool unsure = mn < eps || mx > hm;
+    if (KX) unsure = unsure || mnx < epsx;
+    if (TAB) unsure = unsure || (int)flag < 0;
+    if (__builtin_amdgcn_ballot_w64(unsure)) {
+      const int n4 = FULL ? 4 : n;
+      skip += (uint32_t)n4;
+#pragma unroll 1
+      for (int u = 0; u < n4; u++)
+        wp_record<KX != 0>(P, A, L, jmin, lane, rx, ry, rz, ra, U, j + u, tab32, sE, tabx, sEx,
+                           nrechk);
+      return;
+    }
+#pragma unroll
+    for (int k = 0; k < KX; k++) nx[k] += sx[k];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      if (!FULL && u >= n) break;
+      if ((TAB ? v[u] : d[u]) < top && fabsf(dz[u]) < phi && (!OWN || j + u > jmin)) {
+        // the row m edges below the base, pi bin floor(|f|)
+        const uint32_t base = TAB ? hi + e[u].y : hi;
+        uint32_t x;
+        asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(x) : "v"(m[u]), "v"(nrow4), "v"(base));
+        atomicAdd(lds_ptr(lshl_add((uint32_t)fabsf(f[u]), lsh, x)), 1u);
+      }
+      if (XT && s[u] < topx && (!OWN || j + u > jmin))
+        atomicAdd(lds_ptr(hx + ex[u].y - (ex[u].x << 7)), 1u);
+    }
+  };
+  sfloat *p = (sfloat *)(U.strm + U.jb);
+  int j = U.jb;
+  float a[16];
+  CP_LOAD16(a, p);
+  for (; j + 8 <= U.je; j += 8, p += 32) {
+    float g[16];
+    CP_LOAD16(g, p + 16);
+    rows4(j, a, std::true_type(), 4);
+    CP_LOAD16(a, p + 32);
+    rows4(j + 4, g, std::true_type(), 4);
+  }
+  while (j < U.je) {
+    float g[16];
+    CP_LOAD16(g, p + 16);
+    rows4(j, a, std::false_type(), min(4, U.je - j));
+#pragma unroll
+    for (int t = 0; t < 16; t++) a[t] = g[t];
+    j += 4;
+    p += 16;
+  }
+  if (KX > 0) {
+    // nx[k]: pairs below xi edge xlo + k
+    const uint32_t all = (uint32_t)(U.je - U.jb) - skip;
+    uint32_t *hr = A.histx + (lane & 31);
+    if (xlo >= 1) atomicAdd(hr + xlo * 32, nx[0]);
+#pragma unroll
+    for (int k = 1; k < KX; k++) atomicAdd(hr + (xlo + k) * 32, nx[k] - nx[k - 1]);
+    if (xlo + KX <= P.nbx) atomicAdd(hr + (xlo + KX) * 32, all - nx[NX - 1]);
+  }
 }
 
 // wp, weighted: every in-range pair is evaluated in binary64 for its rp.
@@ -1221,19 +1310,28 @@ void k_pairs(PairParams P) {
   const int lane = threadIdx.x & 63;
   const int wid = threadIdx.x >> 6;
   const int n32 = (PREC == F32R && !xi_f32_weighted(MODE, PREC, W)) ? P.tab32_hi - P.tab32_lo + 1 : 0;
-  const int n64 = P.tab64_hi - P.tab64_lo + 1;
+  const int n64 = few_edge_tables(MODE, PREC, W) ? 0 : P.tab64_hi - P.tab64_lo + 1;
   const int nx = MODE == WPXI ? P.tabx_hi - P.tabx_lo + 1 : 0;
   const LdsLayout LY = lds_layout(MODE, PREC, W, n32, n64, P.nb, P.npi, P.wpc, nx, P.nbx);
   uint2 *tab32 = (uint2 *)(smem + LY.tab32);
   uint2 *tab64 = (uint2 *)(smem + LY.tab64);
   double *sE = (double *)(smem + LY.E);
-  for (int t = threadIdx.x; t < n32; t += blockDim.x) tab32[t] = P.tab32[t];
+  // (few-edge tables: counter rows become byte offsets)
+  constexpr bool FEW = few_edge_tables(MODE, PREC, W);
+  for (int t = threadIdx.x; t < n32; t += blockDim.x) {
+    uint2 e = P.tab32[t];
+    if (FEW) e.y = (e.y & 0x80000000u) | (e.y & 63u) * (uint32_t)(P.npi * P.wpc * 4);
+    tab32[t] = e;
+  }
   for (int t = threadIdx.x; t < n64; t += blockDim.x) tab64[t] = P.tab64[t];
   for (int t = threadIdx.x; t <= P.nb; t += blockDim.x) sE[t] = P.E[t];
   uint2 *tabx = (uint2 *)(smem + LY.tabx);
   double *sEx = (double *)(smem + LY.Ex);
   if (MODE == WPXI) {
-    for (int t = threadIdx.x; t < nx; t += blockDim.x) tabx[t] = P.tabx[t];
+    for (int t = threadIdx.x; t < nx; t += blockDim.x) {
+      const uint2 e = P.tabx[t];
+      tabx[t] = make_uint2(e.x, (e.y & 0x80000000u) | (e.y & 63u) << 7);
+    }
     for (int t = threadIdx.x; t <= P.nbx; t += blockDim.x) sEx[t] = P.Ex[t];
   }
   unsigned char *wb = smem + LY.common + (size_t)wid * LY.wave_bytes;
@@ -1394,10 +1492,16 @@ void k_pairs(PairParams P) {
               ok = false;
               pruned = 1;
             } else {
+              const double rpM = M[0] * M[0] + M[1] * M[1];
               if (MODE == XI) {
-                const double slo = rp + m[2] * m[2];
-                const double shi = (M[0] * M[0] + M[1] * M[1]) + M[2] * M[2];
+                const double slo = rp + m[2] * m[2], shi = rpM + M[2] * M[2];
                 slots = exact_slot(sE, P.nb, slo) | (exact_slot(sE, P.nb, shi) << 8);
+              } else if (PREC == F32R && !W) {
+                // r_p slots, and (WPXI) xi slots in the next two bytes
+                slots = exact_slot_top(sE, P.nb, rp) | (exact_slot_top(sE, P.nb, rpM) << 8);
+                if (MODE == WPXI)
+                  slots |= exact_slot_top(sEx, P.nbx, rp + m[2] * m[2]) << 16 |
+                           exact_slot_top(sEx, P.nbx, rpM + M[2] * M[2]) << 24;
               }
               // z-window of the unit in the cell's own coordinates (Section
               // 2.2, late entry / early exit): a pair within reach has
@@ -1546,12 +1650,38 @@ void k_pairs(PairParams P) {
             }
           } else if (MODE == WPXI) {
             const float ra = __builtin_fmaf(ryf, ryf, rxf * rxf);
-            if (own) loop_wpxi_f32<true>(P, A, L, lane, rxf, ryf, rzf, ra, U, tab32, sE, tabx, sEx, nrechk);
-            else loop_wpxi_f32<false>(P, A, L, lane, rxf, ryf, rzf, ra, U, tab32, sE, tabx, sEx, nrechk);
+            const int kw = U.slot_hi - U.slot_lo;
+            const int xlo = (sl >> 16) & 255, kx = (int)(((unsigned)sl >> 24) - (unsigned)xlo);
+            // xi: no pair below the last edge, one slot (counted at once), up
+            // to three edges, or more
+            const bool sure = !own && !P.noprune, none = sure && xlo > P.nbx;
+            const bool once = sure && !none && kx == 0;
+            if (once && xlo >= 1 && valid) atomicAdd(&A.histx[xlo * 32 + (lane & 31)], (uint32_t)nj);
+            const int kk = none || once ? 0 : kx;
+#define CP_WX(K, KX, O) loop_wp_f32<K, KX, O>(P, A, L, lane, rxf, ryf, rzf, ra, U, xlo, tab32, sE, tabx, sEx, nrechk)
+#define CP_WXK(K) { if (kk == 0) CP_WX(K, 0, false); else if (kk == 1) CP_WX(K, 1, false); \
+                    else if (kk == 2) CP_WX(K, 2, false); else CP_WX(K, 3, false); }
+            if (valid) {
+              if (own) CP_WX(0, -1, true);
+              else if (sure && kw <= 3 && U.slot_hi >= 1 && kk <= 3) {
+                if (kw <= 1) CP_WXK(1) else if (kw == 2) CP_WXK(2) else CP_WXK(3)
+              } else if (kk == 0 && sure) CP_WX(0, 0, false);
+              else CP_WX(0, -1, false);
+            }
+#undef CP_WXK
+#undef CP_WX
           } else if (!W) {
             const float ra = __builtin_fmaf(ryf, ryf, rxf * rxf);
-            if (own) loop_wp_f32<true, true>(P, A, L, lane, rxf, ryf, rzf, ra, U, tab32, sE, nrechk);
-            else loop_wp_f32<false, true>(P, A, L, lane, rxf, ryf, rzf, ra, U, tab32, sE, nrechk);
+            const int kw = U.slot_hi - U.slot_lo;
+#define CP_WF(K, O) loop_wp_f32<K, 0, O>(P, A, L, lane, rxf, ryf, rzf, ra, U, 0, tab32, sE, tabx, sEx, nrechk)
+            if (valid) {
+              if (own) CP_WF(0, true);
+              else if (kw > 3 || P.noprune || U.slot_hi < 1) CP_WF(0, false);
+              else if (kw <= 1) CP_WF(1, false);
+              else if (kw == 2) CP_WF(2, false);
+              else CP_WF(3, false);
+            }
+#undef CP_WF
           } else {
             // weighted: every in-range pair takes the binary64 separation,
             // where the shift costs an add per axis
@@ -1587,7 +1717,7 @@ void k_pairs(PairParams P) {
               else loop_xi_f64_two<false>(P, A, L, lane, U, sE);
             }
           }
-        } else {
+        } else if (!few_edge_tables(MODE, PREC, W)) {
 #define CP_F64(O, SH, WR) loop_f64<MODE, O, SH, WR, W>(P, A, L, lane, U, wrapax, box, half, tab64, sE)
           if (anywrap) {
             if (own) CP_F64(true, true, true); else CP_F64(false, true, true);
