@@ -14,6 +14,10 @@ SOURCES = ["api.hip", "grid_kernels.hip", "pair_kernels.hip", "estimators.cpp", 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    # the SLP vectorizer would turn four records' scalar chains into vectors
+    # with a copy of every lane constant per element: 456 spilled registers in
+    # the binary32 xi kernel at 7 waves per SIMD instead of 21
+    "-fno-slp-vectorize",
     # binary64 separations must follow the reference operation sequence:
     # no multiply-add contraction anywhere (binary32 FMAs are explicit)
     "-ffp-contract=off",

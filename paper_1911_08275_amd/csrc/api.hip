@@ -222,24 +222,15 @@ static void build_few(const EdgeD &E, double eps, const Table &T, int shift, Tab
   F.hi = T.hi;
   F.e.assign(T.hi - T.lo + 1, make_uint2(0, 0));
   const double w = eps * (1.0 + 1e-6) + 1e-37;
+  const int n = E.size();
+  int a = E[0] == 0.0 ? 1 : 0, b = a;   // (s >= 0 = E_0 always); edges a .. b - 1 are near
   for (int m = T.lo; m <= T.hi; m++) {
     const double lo = m == T.lo ? -INFINITY : (double)bitsf((uint32_t)m << shift);
     const double hi = m == T.hi ? INFINITY : (double)bitsf((uint32_t)(m + 1) << shift);
-    int near = 0, last = 0, below = 0;
-    for (int k = 0; k < E.size(); k++) {
-      // (s >= 0 = E_0 always)
-      if (E[k] == 0.0) { below++; continue; }
-      if (E[k] + w >= lo && E[k] - w <= hi) {
-        near++;
-        last = k;
-      } else if (E[k] < lo) {
-        below++;
-      }
-    }
-    uint2 e;
-    if (near == 1) e = make_uint2(fbits((float)E[last]), (uint32_t)(last + 1));
-    else e = make_uint2(fbits(kNegBig), (uint32_t)below | (near ? 0x80000000u : 0u));
-    F.e[m - T.lo] = e;
+    while (a < n && E[a] + w < lo) a++;
+    while (b < n && E[b] - w <= hi) b++;
+    if (b - a == 1) F.e[m - T.lo] = make_uint2(fbits((float)E[a]), (uint32_t)b);
+    else F.e[m - T.lo] = make_uint2(fbits(kNegBig), (uint32_t)a | (b > a ? 0x80000000u : 0u));
   }
 }
 
@@ -701,7 +692,7 @@ static int wp_copies(int mode, int prec, int weighted, int n32, int n64, int nb,
   }
   for (int c = 8; c > 1; c >>= 1) {
     const LdsLayout L = lds_layout(mode, prec, weighted, n32, n64, nb, npi, c, nx, nbx);
-    if (L.common + 4 * L.wave_bytes + kStaticLds <= (size_t)160 * 1024 / 5) return c;
+    if (L.common + 4 * L.wave_bytes + kStaticLds <= (size_t)160 * 1024 / pair_waves(mode, prec, weighted)) return c;
   }
   return 1;
 }
@@ -834,7 +825,7 @@ static int make_binning(int mode, int prec, const double *edges, int nedges, dou
   B.eps32_3 = f32_up(B.bnd.eps + 2.0 * std::ldexp(1.0, -24) * EB * 1.01);
   B.C32 = C32;
   B.A32 = A32;
-  if (mode == WP && prec == F32R) build_few(B.E, B.eps32_3, B.t32, B.shift, B.few);
+  if (prec == F32R) build_few(B.E, B.eps32_3, B.t32, B.shift, B.few);
   B.dpi = mode == WP ? pimax / npi : 1.0;
   if (mode == WP) {
     const double u = std::ldexp(1.0, -24);

@@ -229,7 +229,26 @@ __host__ __device__ constexpr bool xi_f32_weighted(int mode, int prec, int weigh
 // wp_record) and which run no binary64 loop, hence hold no binary64 table: a
 // grid with a wrapped axis runs binary64 kernels.
 __host__ __device__ constexpr bool few_edge_tables(int mode, int prec, int weighted) {
-  return mode != XI && prec == F32R && !weighted;
+  return prec == F32R && !weighted;
+}
+// Columns of a wave's xi counters, one per pair of lanes (lane mod 32: LDS takes
+// a wave's atomics 32 lanes at a time, so the pair never meets); one per lane
+// would leave LDS for five waves per SIMD only.
+constexpr int kXiCols = 32;
+// Waves per SIMD that the pair kernel's register allocation aims at (7: 72
+// VGPRs, 6: 80, 5: 96, 4: 128).  The loops wait on scalar loads of the streamed
+// records, so more waves are faster until the allocation spills inside them:
+// pair kernel at 5 / 6 / 7 waves, in ms: xi of 10^6 and 10^7 binary32 points
+// 9.8 / 8.8 / 8.2 (8: 8.1, but 10^6 points 0.68 to 0.77), weighted xi of 10^6
+// binary64 points 1.49 / 1.46 / 1.48, w_p of 10^6 binary32 points 1.55 / 1.48 /
+// 1.66, fused w_p and xi of 16 catalogues 48.6 / 59.2 / 74.5; the rest the same.
+// Weighted xi with the binary32 filter holds a pair list per wave and fits
+// four workgroups per CU in LDS.
+__host__ __device__ constexpr int pair_waves(int mode, int prec, int weighted) {
+  return xi_f32_weighted(mode, prec, weighted) ? 4
+         : mode == XI && prec == F32R          ? 7
+         : mode == XI && weighted              ? 6
+         : mode == WP && prec == F32R && !weighted ? 6 : 5;
 }
 // List entries per wave: fewer than 64 are left over after a drain, and a
 // group of four records adds at most 4 x 64.
@@ -261,7 +280,7 @@ __host__ __device__ inline LdsLayout lds_layout(int mode, int prec, int weighted
   }
   L.common = align16(off);
   const int NS = nb + 2;
-  const size_t words = mode == XI ? (size_t)NS * 64 : (size_t)NS * npi * wpc;
+  const size_t words = mode == XI ? (size_t)NS * kXiCols : (size_t)NS * npi * wpc;
   L.wave_hist = align16(words * 4);
   // weight sums are shared by the wave (one row of slots), not lane-private
   L.wave_w = weighted ? (mode == XI ? (size_t)NS * kWStripe : words) * 8 : 0;

@@ -244,23 +244,14 @@ __device__ inline void flush_xi_rows(uint32_t *rows, unsigned long long *gh, int
     for (int s = 0; s < nb + 2; s++) rows[s * 32 + lane] = 0u;
 }
 
-template <int MODE, int W>
+template <int MODE, int PREC, int W>
 __device__ inline void flush_hist(const PairParams &P, WaveArea A, int mock, int lane) {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
   const int nb = P.nb, NS = P.nslots;
   unsigned long long *gh = P.hist + (int64_t)mock * P.hist_stride;
   if (MODE == XI) {
-    // lane s - 1 takes slot s's wave total, and one atomic instruction adds
-    // them all: every wave's totals land in the same few lines of the output,
-    // and per-slot atomics from one lane (one memory request each) queued
-    // there for tens of microseconds at the end of a launch
-    unsigned long long mine = 0;
-    for (int s = 1; s <= nb; s++) {
-      const unsigned long long v = wave_sum_u64((unsigned long long)A.hist[s * 64 + lane]);
-      if (lane == s - 1) mine = v;
-    }
-    if (lane < nb && mine) atomicAdd(gh + lane, mine);
+    flush_xi_rows(A.hist, gh, nb, lane);
     if (W && lane >= 1 && lane <= nb) {
       double a = 0.0, b = 0.0;
       for (int c = 0; c < kWStripe; c++) {
@@ -272,7 +263,6 @@ __device__ inline void flush_hist(const PairParams &P, WaveArea A, int mock, int
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    for (int s = 0; s < NS; s++) A.hist[s * 64 + lane] = 0u;
     if (W) {
       for (int t = lane; t < 2 * NS * kWStripe; t += 64) A.hw[t] = 0.0;
     }
@@ -351,6 +341,33 @@ __device__ inline void stream_f32(const float4 *base, int jb, int je, F &&body) 
     body(j, r0, r1, r2, r3);
     j++;
     p += 4;
+  }
+}
+
+// The same with the body called once per group of four records, body(j, q,
+// full, n): q their 16 values, full a type that tells whole groups from the
+// last one, which has n records and the values of up to three more.
+template <typename F>
+__device__ inline void stream4_f32(const float4 *base, int jb, int je, F &&body) {
+  sfloat *p = (sfloat *)(base + jb);
+  int j = jb;
+  float a[16];
+  CP_LOAD16(a, p);
+  for (; j + 8 <= je; j += 8, p += 32) {
+    float b[16];
+    CP_LOAD16(b, p + 16);
+    body(j, a, std::true_type(), 4);
+    CP_LOAD16(a, p + 32);
+    body(j + 4, b, std::true_type(), 4);
+  }
+  while (j < je) {
+    float b[16];
+    CP_LOAD16(b, p + 16);
+    body(j, a, std::false_type(), min(4, je - j));
+#pragma unroll
+    for (int t = 0; t < 16; t++) a[t] = b[t];
+    j += 4;
+    p += 16;
   }
 }
 
@@ -490,131 +507,154 @@ __device__ inline void recheck_xi(WaveArea A, const LanePt &L, int lane, const U
   double dx, dy, dz;
   ref_sep<SHIFT, false>(L.x, L.y, L.z, ux, uy, uz, U.S, wrapax, 0.0, 0.0, dx, dy, dz);
   const double s64 = (dx * dx + dy * dy) + dz * dz;
-  atomicAdd(&A.hist[exact_slot(sE, nb, s64) * 64 + lane], 1u);
+  atomicAdd(&A.hist[exact_slot(sE, nb, s64) * kXiCols + (lane & (kXiCols - 1))], 1u);
 }
 
-// xi, binary32, a unit whose pairs can only land in slot_lo or slot_hi:
-// edge E_t (t = slot_lo) decides.  The edge is folded into the lane's
-// constant, b = fl32(|r|^2 - E_t), so three FMAs and one add give
-// d~ = s~ - E_t directly; rounding keeps the sign of the last add, so the
-// decision error is that of the Gram form (the bound eps covers it).  The
-// first pass, branch-free, counts the negative d~ per lane and tracks the
-// smallest |d~|.  Only a lane with some |d~| < eps takes a second pass that
-// re-evaluates the same binary32 values, bit for bit, and sends those pairs
-// to binary64.  exec = valid lanes.
-template <bool SHIFT>
-__device__ inline void loop_xi_f32_two(const PairParams &P, WaveArea A, const LanePt &L, int lane,
+// xi, binary32, a unit whose pairs can only land in K + 1 slots, slot_lo ..
+// slot_lo + K (not an own cell): edges E_k = E[slot_lo + k] decide, k < K.  The
+// first edge is folded into the lane's constant, b = fl32(|r|^2 - E_0), so
+// three FMAs and one add give d_0 = s~ - E_0 directly; rounding keeps the sign
+// of the last add, so the decision error is that of the Gram form (the bound
+// eps32 covers it).  The others follow in one add, d_k = fl(d_0 + fl32(E_0 -
+// E_k)): an add keeps the sign of its exact result, so their decision error is
+// that of d_0 plus u |E_0 - E_k|, which eps32_3 covers.  The first pass,
+// branch-free, counts the negative d_k per lane in registers and tracks the
+// smallest |d_k|.  Only lanes with one below the bound take a second pass that
+// re-evaluates the same binary32 values, bit for bit, and sends those pairs to
+// binary64.  Bound: VALU issue, about 14 + 8 K cycles per 64 pairs (two-operand
+// instructions take two cycles of a wave, others four); the table loop below
+// takes about 50; chains up to K = 3, 4 or 5 were equally fast.  xi of 10^6 binary32 points 1.00
+// (decision tables beyond K = 2, five waves per SIMD) to 0.83 ms a call, 10^6 by
+// 10^7 points 12.9 to 9.9.  exec = valid lanes.
+template <int K>
+__device__ inline void loop_xi_f32_few(const PairParams &P, WaveArea A, const LanePt &L, int lane,
                                        float rx, float ry, float rz, float ra, const Unit &U,
                                        const double *sE, uint32_t &nrechk) {
-  const int nb = P.nb;
-  const float b = (float)((double)ra - sE[U.slot_lo]);
-  const float eps = P.eps32;
-  uint32_t nneg = 0;
+  const int nb = P.nb, k0 = U.slot_lo;
+  const double E0 = sE[k0];
+  const float b = (float)((double)ra - E0);
+  float c[K];
+  c[0] = 0.f;
+#pragma unroll
+  for (int k = 1; k < K; k++) c[k] = (float)(E0 - sE[k0 + k]);
+  const float eps = K == 1 ? P.eps32 : P.eps32_3;
+  uint32_t n[K];
+#pragma unroll
+  for (int k = 0; k < K; k++) n[k] = 0;
   float mn = 3.0e38f;
-  stream_f32(U.strm, U.jb, U.je, [&](int, float qx, float qy, float qz, float qw) {
-    const float d = gram3(rx, ry, rz, b, qx, qy, qz, qw);
-    nneg += __float_as_uint(d) >> 31;
-    mn = fminf(mn, fabsf(d));
-  });
-  uint32_t uneg = 0, upos = 0;
-  if (mn < eps) {
-    stream_f32(U.strm, U.jb, U.je, [&](int j, float qx, float qy, float qz, float qw) {
-      const float d = gram3(rx, ry, rz, b, qx, qy, qz, qw);
-      if (fabsf(d) < eps) {
-        recheck_xi<SHIFT>(A, L, lane, U, j, sE, nb);
-        const uint32_t ng = __float_as_uint(d) >> 31;
-        uneg += ng;
-        upos += 1u - ng;
+  stream4_f32(U.strm, U.jb, U.je, [&](int, const float *q, auto full, int cnt) {
+#pragma unroll
+    for (int u = 0; u < 4; u += 2) {
+      float d[2 * K];
+      if (!decltype(full)::value && u >= cnt) break;
+      const bool both = decltype(full)::value || u + 1 < cnt;
+#pragma unroll
+      for (int v = 0; v < 2; v++) {
+        if (v && !both) break;
+        const float d0 = gram3(rx, ry, rz, b, q[4 * (u + v)], q[4 * (u + v) + 1],
+                               q[4 * (u + v) + 2], q[4 * (u + v) + 3]);
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+          d[v * K + k] = k ? d0 + c[k] : d0;
+          n[k] += __float_as_uint(d[v * K + k]) >> 31;
+        }
       }
-    });
-    nrechk += uneg + upos;
-  }
-  const uint32_t nlo = nneg - uneg;
-  const uint32_t nhi = (uint32_t)(U.je - U.jb) - nneg - upos;
-  if (U.slot_lo >= 1) atomicAdd(&A.hist[U.slot_lo * 64 + lane], nlo);
-  if (U.slot_hi <= nb) atomicAdd(&A.hist[U.slot_hi * 64 + lane], nhi);
-}
-
-// xi, binary32, a unit whose pairs can only land in slot_lo, slot_lo + 1 or
-// slot_lo + 2: edges E_a = E[slot_lo] and E_b = E[slot_lo + 1] decide.
-// d1 = s~ - E_a comes from the folded Gram form as in the two-slot loop and
-// d2 = fl(d1 + fl32(E_a - E_b)) from it in one add; the add keeps the sign of
-// its exact result, so d2's decision error is that of d1 plus u |E_a - E_b|,
-// which eps32_3 covers.  Sign counts give the three slot counts; lanes with
-// a |d| below the bound re-evaluate those pairs in a second pass.
-// exec = valid lanes.
-template <bool SHIFT>
-__device__ inline void loop_xi_f32_three(const PairParams &P, WaveArea A, const LanePt &L,
-                                         int lane, float rx, float ry, float rz, float ra,
-                                         const Unit &U, const double *sE, uint32_t &nrechk) {
-  const int nb = P.nb;
-  const double Ea = sE[U.slot_lo], Eb = sE[U.slot_lo + 1];
-  const float b = (float)((double)ra - Ea);
-  const float c = (float)(Ea - Eb);
-  const float eps = P.eps32_3;
-  uint32_t n1 = 0, n2 = 0;
-  float mn = 3.0e38f;
-  stream_f32(U.strm, U.jb, U.je, [&](int, float qx, float qy, float qz, float qw) {
-    const float d1 = gram3(rx, ry, rz, b, qx, qy, qz, qw);
-    const float d2 = d1 + c;
-    n1 += __float_as_uint(d1) >> 31;
-    n2 += __float_as_uint(d2) >> 31;
-    mn = fminf(mn, fminf(fabsf(d1), fabsf(d2)));
+      if (both) {
+#pragma unroll
+        for (int k = 0; k < K; k++) mn = fminf(mn, fminf(fabsf(d[2 * k]), fabsf(d[2 * k + 1])));
+      } else {
+#pragma unroll
+        for (int k = 0; k < K; k++) mn = fminf(mn, fabsf(d[k]));
+      }
+    }
   });
-  uint32_t u1 = 0, u2 = 0, un = 0;
+  uint32_t un = 0;
   if (mn < eps) {
     stream_f32(U.strm, U.jb, U.je, [&](int j, float qx, float qy, float qz, float qw) {
-      const float d1 = gram3(rx, ry, rz, b, qx, qy, qz, qw);
-      const float d2 = d1 + c;
-      if (fabsf(d1) < eps || fabsf(d2) < eps) {
-        recheck_xi<SHIFT>(A, L, lane, U, j, sE, nb);
-        u1 += __float_as_uint(d1) >> 31;
-        u2 += __float_as_uint(d2) >> 31;
+      const float d0 = gram3(rx, ry, rz, b, qx, qy, qz, qw);
+      float m1 = fabsf(d0);
+#pragma unroll
+      for (int k = 1; k < K; k++) m1 = fminf(m1, fabsf(d0 + c[k]));
+      if (m1 < eps) {
+        recheck_xi<true>(A, L, lane, U, j, sE, nb);
+#pragma unroll
+        for (int k = 0; k < K; k++) n[k] -= __float_as_uint(k ? d0 + c[k] : d0) >> 31;
         un++;
       }
     });
     nrechk += un;
   }
-  const uint32_t c0 = n1 - u1;                       // below E_a
-  const uint32_t c1 = (n2 - u2) - c0;                // [E_a, E_b)
-  const uint32_t c2 = (uint32_t)(U.je - U.jb) - un - (n2 - u2);   // at or above E_b
-  if (U.slot_lo >= 1) atomicAdd(&A.hist[U.slot_lo * 64 + lane], c0);
-  atomicAdd(&A.hist[(U.slot_lo + 1) * 64 + lane], c1);
-  if (U.slot_lo + 2 <= nb) atomicAdd(&A.hist[(U.slot_lo + 2) * 64 + lane], c2);
+  // n[k]: certain pairs below edge k0 + k
+  uint32_t *h = A.hist + k0 * kXiCols + (lane & (kXiCols - 1));
+  if (k0 >= 1) atomicAdd(h, n[0]);
+#pragma unroll
+  for (int k = 1; k < K; k++) atomicAdd(h + kXiCols * k, n[k] - n[k - 1]);
+  if (k0 + K <= nb) atomicAdd(h + kXiCols * K, (uint32_t)(U.je - U.jb) - un - n[K - 1]);
 }
 
-// xi, binary32, general unit: per-lane table lookup.  OWN: one of the tile's
-// own cells (auto-count), only j > i pairs.  An uncertain pair is
-// re-evaluated in binary64 on the spot: the branch is taken on the few
-// records where some lane has one, which costs less than streaming the unit
-// a second time (measured).
-template <bool OWN, bool SHIFT>
+// One record of the loop below, pair by pair.
+template <bool OWN>
+__device__ inline void xi_record(const PairParams &P, WaveArea A, const LanePt &L, int lane,
+                                 float rx, float ry, float rz, float ra, const Unit &U, int j,
+                                 const uint2 *tab32, const double *sE, uint32_t &nrechk) {
+  sfloat *q = (sfloat *)(U.strm + j);
+  const float v = gram3(rx, ry, rz, ra, q[0], q[1], q[2], q[3]);
+  if (v < P.AB32 && (!OWN || j > L.iloc)) {
+    const uint2 e = tab32[min(max(__float_as_int(v) >> P.tab_shift, P.tab32_lo), P.tab32_hi) - P.tab32_lo];
+    const float d = v - __uint_as_float(e.x);
+    if (fabsf(d) < P.eps32_3 || (int)e.y < 0) {
+      recheck_xi<true>(A, L, lane, U, j, sE, P.nb);
+      nrechk++;
+    } else {
+      atomicAdd(lds_ptr(lds_addr(A.hist) + 4u * (uint32_t)(lane & (kXiCols - 1)) + e.y -
+                        (d < 0.f ? 4u * kXiCols : 0u)), 1u);
+    }
+  }
+}
+
+// xi, binary32, general unit: one edge per pair from the few-edge table (see
+// below, w_p), the pair's slot from the sign of its difference.  OWN: one of
+// the tile's own cells (auto-count), only j > i pairs.  Four records share the
+// test for uncertain pairs; they then go pair by pair.  exec = valid lanes.
+template <bool OWN>
 __device__ inline void loop_xi_f32(const PairParams &P, WaveArea A, const LanePt &L, int lane,
                                    float rx, float ry, float rz, float ra, const Unit &U,
                                    const uint2 *tab32, const double *sE, uint32_t &nrechk) {
-  const float AB = P.AB32;
-  const int lo = P.tab32_lo, sh = P.tab_shift;
-  const uint2 *tb = tab32 - lo;   // s~ < AB32, the table's top: clamped below only
-  const int nb = P.nb;
-  uint32_t nunc = 0;
-  stream_f32(U.strm, U.jb, U.je, [&](int j, float qx, float qy, float qz, float qw) {
-    const float s = gram3(rx, ry, rz, ra, qx, qy, qz, qw);
-    bool inr = s < AB;
-    if (OWN) inr = inr && (j > L.iloc);
-    if (inr) {
-      const uint2 e = tb[max(__float_as_int(s) >> sh, lo)];
-      const bool ch = s >= __uint_as_float(e.y);
-      TabHit h;
-      h.unc = (s >= __uint_as_float(e.x)) && !ch;
-      h.slot = (int)(e.y & 63u) - 1 + (ch ? 1 : 0);
-      if (!h.unc) atomicAdd(&A.hist[h.slot * 64 + lane], 1u);
-      else {
-        recheck_xi<SHIFT>(A, L, lane, U, j, sE, nb);
-        nunc++;
-      }
+  const int lo = in_vgpr(P.tab32_lo), hi = in_vgpr(P.tab32_hi), sh = in_vgpr(P.tab_shift);
+  const uint2 *tb = tab32 - P.tab32_lo;
+  const float AB = in_vgpr(P.AB32), eps = in_vgpr(P.eps32_3);
+  const uint32_t hl = lds_addr(A.hist) + 4u * (uint32_t)(lane & (kXiCols - 1));
+  stream4_f32(U.strm, U.jb, U.je, [&](int j, const float *q, auto full, int cnt) {
+    constexpr bool FULL = decltype(full)::value;
+    float v[4], d[4], mn = 3.0e38f;
+    uint2 e[4];
+    uint32_t flag = 0;
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      v[u] = gram3(rx, ry, rz, ra, q[4 * u], q[4 * u + 1], q[4 * u + 2], q[4 * u + 3]);
+      e[u] = tb[min(max(__float_as_int(v[u]) >> sh, lo), hi)];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      d[u] = v[u] - __uint_as_float(e[u].x);
+      mn = fminf(mn, fabsf(d[u]));
+      flag |= e[u].y;
+    }
+    if (__builtin_amdgcn_ballot_w64(mn < eps || (int)flag < 0)) {
+      const int n4 = FULL ? 4 : cnt;
+#pragma unroll 1
+      for (int u = 0; u < n4; u++)
+        xi_record<OWN>(P, A, L, lane, rx, ry, rz, ra, U, j + u, tab32, sE, nrechk);
+      return;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      if (!FULL && u >= cnt) break;
+      if (v[u] < AB && (!OWN || j + u > L.iloc))
+        atomicAdd(lds_ptr(lshl_add((uint32_t)((int)__float_as_uint(d[u]) >> 31), 7u, hl + e[u].y)),
+                  1u);
     }
   });
-  nrechk += nunc;
 }
 
 // wp, binary32 filter (the loops below): the r_p^2 estimate v~ (Gram form in
@@ -822,26 +862,7 @@ __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt
         atomicAdd(lds_ptr(hx + ex[u].y - (ex[u].x << 7)), 1u);
     }
   };
-  sfloat *p = (sfloat *)(U.strm + U.jb);
-  int j = U.jb;
-  float a[16];
-  CP_LOAD16(a, p);
-  for (; j + 8 <= U.je; j += 8, p += 32) {
-    float g[16];
-    CP_LOAD16(g, p + 16);
-    rows4(j, a, std::true_type(), 4);
-    CP_LOAD16(a, p + 32);
-    rows4(j + 4, g, std::true_type(), 4);
-  }
-  while (j < U.je) {
-    float g[16];
-    CP_LOAD16(g, p + 16);
-    rows4(j, a, std::false_type(), min(4, U.je - j));
-#pragma unroll
-    for (int t = 0; t < 16; t++) a[t] = g[t];
-    j += 4;
-    p += 16;
-  }
+  stream4_f32(U.strm, U.jb, U.je, rows4);
   if (KX > 0) {
     // nx[k]: pairs below xi edge xlo + k
     const uint32_t all = (uint32_t)(U.je - U.jb) - skip;
@@ -985,7 +1006,7 @@ __device__ inline void loop_xi_f32_w(const PairParams &P, WaveArea A, int lane, 
       if (v) {
         const int slot = slot64(tab64, P.tab64_lo, P.tab64_hi, P.tab_shift, sE, nb, s);
         const double ww = pt.w * pq.w;
-        atomicAdd(&A.hist[slot * 64 + lane], 1u);
+        atomicAdd(&A.hist[slot * kXiCols + (lane & (kXiCols - 1))], 1u);
         add_w(A.hw + 2 * (slot * kWStripe + st), ww, ww * r);
         nout += slot > nb ? 1u : 0u;
       }
@@ -1071,11 +1092,11 @@ __device__ inline void loop_xi_f32_w(const PairParams &P, WaveArea A, int lane, 
     // listed pairs that binary64 placed at or beyond E_B
     const unsigned long long kept = wave_sum_u64((unsigned long long)(c1 + c2));
     if (lane == 0) nrechk += (uint32_t)(listed - (int)kept);
-    atomicAdd(&A.hist[nb * 64 + lane], c1);
+    atomicAdd(&A.hist[nb * kXiCols + (lane & (kXiCols - 1))], c1);
     add_w(A.hw + 2 * (nb * kWStripe + st), w1, r1);
   }
   if (CLS == 2 && nb > 1) {
-    atomicAdd(&A.hist[(nb - 1) * 64 + lane], c2);
+    atomicAdd(&A.hist[(nb - 1) * kXiCols + (lane & (kXiCols - 1))], c2);
     add_w(A.hw + 2 * ((nb - 1) * kWStripe + st), w2, r2);
   }
 }
@@ -1097,8 +1118,8 @@ __device__ inline void loop_xi_f64_two(const PairParams &P, WaveArea A, const La
     chi += s64 >= Et ? 1u : 0u;
   });
   const uint32_t clo = (uint32_t)(U.je - U.jb) - chi;
-  if (U.slot_lo >= 1) atomicAdd(&A.hist[U.slot_lo * 64 + lane], clo);
-  if (U.slot_hi <= nb) atomicAdd(&A.hist[U.slot_hi * 64 + lane], chi);
+  if (U.slot_lo >= 1) atomicAdd(&A.hist[U.slot_lo * kXiCols + (lane & (kXiCols - 1))], clo);
+  if (U.slot_hi <= nb) atomicAdd(&A.hist[U.slot_hi * kXiCols + (lane & (kXiCols - 1))], chi);
 }
 
 // Weighted xi, binary64, two-slot unit (register sums of w_j and w_j r per
@@ -1133,11 +1154,11 @@ __device__ inline void loop_xi_f64_two_w(const PairParams &P, WaveArea A, const 
   });
   const uint32_t nlo = (uint32_t)(U.je - U.jb) - nhi;
   if (U.slot_lo >= 1) {
-    atomicAdd(&A.hist[U.slot_lo * 64 + lane], nlo);
+    atomicAdd(&A.hist[U.slot_lo * kXiCols + (lane & (kXiCols - 1))], nlo);
     add_w(A.hw + 2 * (U.slot_lo * kWStripe + (lane & (kWStripe - 1))), L.w * wlo, L.w * rlo);
   }
   if (HIREAL) {
-    atomicAdd(&A.hist[U.slot_hi * 64 + lane], nhi);
+    atomicAdd(&A.hist[U.slot_hi * kXiCols + (lane & (kXiCols - 1))], nhi);
     add_w(A.hw + 2 * (U.slot_hi * kWStripe + (lane & (kWStripe - 1))), L.w * whi, L.w * rhi);
   }
 }
@@ -1188,13 +1209,13 @@ __device__ inline void loop_xi_f64_three(const PairParams &P, WaveArea A, const 
   const uint32_t n1 = (uint32_t)(U.je - U.jb) - n0 - n2;
   const int st = lane & (kWStripe - 1);
   if (s0 >= 1) {
-    atomicAdd(&A.hist[s0 * 64 + lane], n0);
+    atomicAdd(&A.hist[s0 * kXiCols + (lane & (kXiCols - 1))], n0);
     if (W) add_w(A.hw + 2 * (s0 * kWStripe + st), L.w * w0, L.w * r0);
   }
-  atomicAdd(&A.hist[(s0 + 1) * 64 + lane], n1);
+  atomicAdd(&A.hist[(s0 + 1) * kXiCols + (lane & (kXiCols - 1))], n1);
   if (W) add_w(A.hw + 2 * ((s0 + 1) * kWStripe + st), L.w * w1, L.w * r1);
   if (s0 + 2 <= nb) {
-    atomicAdd(&A.hist[(s0 + 2) * 64 + lane], n2);
+    atomicAdd(&A.hist[(s0 + 2) * kXiCols + (lane & (kXiCols - 1))], n2);
     if (W) add_w(A.hw + 2 * ((s0 + 2) * kWStripe + st), L.w * w2, L.w * r2);
   }
 }
@@ -1218,7 +1239,7 @@ __device__ inline void loop_f64(const PairParams &P, WaveArea A, const LanePt &L
       if (OWN) inr = inr && (j > L.iloc);
       if (inr) {
         const int slot = slot64_below(tb, lo, sh, sE, nb, s64);
-        atomicAdd(&A.hist[slot * 64 + lane], 1u);
+        atomicAdd(&A.hist[slot * kXiCols + (lane & (kXiCols - 1))], 1u);
         if (W) {
           const double ww = L.w * uw;
           add_w(A.hw + 2 * (slot * kWStripe + (lane & (kWStripe - 1))), ww, ww * sep_sqrt(s64));
@@ -1294,15 +1315,8 @@ struct ItemQueue {
   }
 };
 
-// Waves per SIMD the register allocation aims at: five (96 VGPRs) for most
-// instances; weighted xi with the binary32 filter holds a pair list per wave
-// and fits four workgroups per CU in LDS, so it takes the 128 VGPRs of four.
-template <int MODE, int PREC, int W> struct PairOcc {
-  static constexpr int waves = xi_f32_weighted(MODE, PREC, W) ? 4 : 5;
-};
-
 template <int MODE, int PREC, int W>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PairOcc<MODE, PREC, W>::waves)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pair_waves(MODE, PREC, W))))
 void k_pairs(PairParams P) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ uint32_t qdrained;   // see ItemQueue
@@ -1320,7 +1334,7 @@ void k_pairs(PairParams P) {
   constexpr bool FEW = few_edge_tables(MODE, PREC, W);
   for (int t = threadIdx.x; t < n32; t += blockDim.x) {
     uint2 e = P.tab32[t];
-    if (FEW) e.y = (e.y & 0x80000000u) | (e.y & 63u) * (uint32_t)(P.npi * P.wpc * 4);
+    if (FEW) e.y = (e.y & 0x80000000u) | (e.y & 63u) * (MODE == XI ? 4u * kXiCols : (uint32_t)(P.npi * P.wpc * 4));
     tab32[t] = e;
   }
   for (int t = threadIdx.x; t < n64; t += blockDim.x) tab64[t] = P.tab64[t];
@@ -1344,7 +1358,7 @@ void k_pairs(PairParams P) {
     for (int t = lane; t < (P.nbx + 2) * 32; t += 64) A.histx[t] = 0u;
   }
   const int NS = P.nslots;
-  const int hwords = MODE == XI ? NS * 64 : NS * P.npi * P.wpc;
+  const int hwords = MODE == XI ? NS * kXiCols : NS * P.npi * P.wpc;
   const int wwords = MODE == XI ? NS * kWStripe : hwords;
   for (int t = lane; t < hwords; t += 64) A.hist[t] = 0u;
   if (W) {
@@ -1377,7 +1391,7 @@ void k_pairs(PairParams P) {
     const Tile T = P.tiles[tile_ix];
     const int mock = uni(T.mock);
     if (mock != cur_mock) {
-      if (cur_mock >= 0) flush_hist<MODE, W>(P, A, cur_mock, lane);
+      if (cur_mock >= 0) flush_hist<MODE, PREC, W>(P, A, cur_mock, lane);
       cur_mock = mock;
       since_flush = 0;
     }
@@ -1591,13 +1605,14 @@ void k_pairs(PairParams P) {
         st_cells += (unsigned long long)nrun;
         since_flush += nj;
         if (since_flush > flush_limit) {
-          flush_hist<MODE, W>(P, A, cur_mock, lane);
+          flush_hist<MODE, PREC, W>(P, A, cur_mock, lane);
           since_flush = nj;
         }
         // all pairs of the unit in one bin: count them without separations
         if (MODE == XI && !W && !own && !anywrap && !P.noprune && U.slot_lo == U.slot_hi) {
           if (U.slot_lo >= 1 && U.slot_lo <= P.nb && valid)
-            atomicAdd(&A.hist[U.slot_lo * 64 + lane], (uint32_t)nj);
+            atomicAdd(&A.hist[U.slot_lo * kXiCols + (lane & (kXiCols - 1))],
+                      (uint32_t)nj);
           continue;
         }
         st_cand += (unsigned long long)nvalid * nj;
@@ -1640,14 +1655,16 @@ void k_pairs(PairParams P) {
           // kernel, kinder to the instruction cache).
           if (MODE == XI) {
             const float ra = __builtin_fmaf(rzf, rzf, __builtin_fmaf(ryf, ryf, rxf * rxf));
-            if (two) {
-              if (valid) loop_xi_f32_two<true>(P, A, L, lane, rxf, ryf, rzf, ra, U, sE, nrechk);
-            } else if (!own && U.slot_hi == U.slot_lo + 2) {
-              if (valid) loop_xi_f32_three<true>(P, A, L, lane, rxf, ryf, rzf, ra, U, sE, nrechk);
-            } else {
-              if (own) loop_xi_f32<true, true>(P, A, L, lane, rxf, ryf, rzf, ra, U, tab32, sE, nrechk);
-              else loop_xi_f32<false, true>(P, A, L, lane, rxf, ryf, rzf, ra, U, tab32, sE, nrechk);
+            const int kw = U.slot_hi - U.slot_lo;
+#define CP_XF(K) loop_xi_f32_few<K>(P, A, L, lane, rxf, ryf, rzf, ra, U, sE, nrechk)
+            if (valid) {
+              if (own) loop_xi_f32<true>(P, A, L, lane, rxf, ryf, rzf, ra, U, tab32, sE, nrechk);
+              else if (kw == 1) CP_XF(1);
+              else if (kw == 2) CP_XF(2);
+              else if (kw == 3) CP_XF(3);
+              else loop_xi_f32<false>(P, A, L, lane, rxf, ryf, rzf, ra, U, tab32, sE, nrechk);
             }
+#undef CP_XF
           } else if (MODE == WPXI) {
             const float ra = __builtin_fmaf(ryf, ryf, rxf * rxf);
             const int kw = U.slot_hi - U.slot_lo;
@@ -1731,7 +1748,7 @@ void k_pairs(PairParams P) {
       }
     }
   }
-  if (cur_mock >= 0) flush_hist<MODE, W>(P, A, cur_mock, lane);
+  if (cur_mock >= 0) flush_hist<MODE, PREC, W>(P, A, cur_mock, lane);
   const unsigned long long rc = wave_sum_u64((unsigned long long)nrechk);
   // one atomic instruction for the four statistics (lane k adds word k)
   const unsigned long long sv = lane == 0 ? st_cand : lane == 1 ? rc : lane == 2 ? st_cells : st_pruned;

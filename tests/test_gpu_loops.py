@@ -65,6 +65,27 @@ def test_wp_loops(native, name, n, refine):
 
 
 @pytest.mark.parametrize("name", sorted(EDGES))
+@pytest.mark.parametrize("n,refine", [(37, (1, 1, 1)), (3001, (1, 1, 1)), (6007, (3, 3, 2))])
+def test_xi_loops(native, name, n, refine):
+    """Units counted at once, by one to three edges and by the table; 1 to
+    many records, own cells, ties, pruned and not; both precisions (their
+    counters have one column per pair of lanes)."""
+    edges, box = EDGES[name], 31.0
+    cat = _cloud(n, box, 6)
+    ref = oracle.xi(cat, edges, periodic=True, box=box)
+    d = native.to_device(cat)
+    for prec in ("fp64", "fp32"):
+        for noprune in (False, True):
+            _say("xi loops", name, n, refine, prec, noprune)
+            g = native.countpairs_xi(d, edges, precision=prec, periodic=True, boxsize=box,
+                                     refine=refine, no_prune=noprune)
+            assert (g.npairs == ref.npairs).all()
+            assert g.stats["precision"] == prec
+    if n > 3000:
+        assert g.stats["rechecks"] > 0
+
+
+@pytest.mark.parametrize("name", sorted(EDGES))
 @pytest.mark.parametrize("refine", [(1, 1, 1), (3, 3, 2)])
 def test_fused_loops(native, name, refine):
     """w_p and xi in one launch, the xi edges reaching less far than, as far
