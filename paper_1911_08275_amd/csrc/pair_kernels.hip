@@ -316,8 +316,24 @@ constexpr double kNoPoint = 1e200;   // coordinates of the lanes beyond a tile's
 
 #define CP_LOAD16(dst, src)                                                                    \
   _Pragma("unroll") for (int t_ = 0; t_ < 16; t_++) dst[t_] = (src)[t_];
+// The next group's loads, issued before the body of the group at hand: scalar
+// loads return in any order, so a wait for one is a wait for all, and the
+// group at hand is waited for first (left to itself, the compiler issued the
+// loads when the body was nearly through: pair kernel of w_p of 10^6 points
+// 1.48 against 1.44 ms, of 10^6 by 10^7 points 8.1 against 7.8, of 10^6 binary64
+// points at R_max 10 0.36 against 0.35).
+#define CP_AHEAD16(dst, src)                                                                   \
+  wait_scalar_loads();                                                                         \
+  CP_LOAD16(dst, src);                                                                         \
+  __builtin_amdgcn_sched_barrier(0);
 #define CP_REC4(arr, jj, u) body((jj) + (u), arr[4 * (u)], arr[4 * (u) + 1], arr[4 * (u) + 2], \
                                  arr[4 * (u) + 3])
+
+__device__ inline void wait_scalar_loads() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+  __builtin_amdgcn_sched_barrier(0);
+}
 
 template <typename F>
 __device__ inline void stream_f32(const float4 *base, int jb, int je, F &&body) {
@@ -344,9 +360,11 @@ __device__ inline void stream_f32(const float4 *base, int jb, int je, F &&body) 
   }
 }
 
-// The same with the body called once per group of four records, body(j, q,
-// full, n): q their 16 values, full a type that tells whole groups from the
-// last one, which has n records and the values of up to three more.
+// The same with the body called once per group of four records, body(j, q)
+// with q their 16 values.  Records past the unit are replaced (the memory there
+// may hold anything) by one at the frame's origin with |p|^2 = 3.2e38: beyond
+// every edge.
+constexpr float kFarRec = 3.2e38f;
 template <typename F>
 __device__ inline void stream4_f32(const float4 *base, int jb, int je, F &&body) {
   sfloat *p = (sfloat *)(base + jb);
@@ -355,15 +373,23 @@ __device__ inline void stream4_f32(const float4 *base, int jb, int je, F &&body)
   CP_LOAD16(a, p);
   for (; j + 8 <= je; j += 8, p += 32) {
     float b[16];
-    CP_LOAD16(b, p + 16);
-    body(j, a, std::true_type(), 4);
-    CP_LOAD16(a, p + 32);
-    body(j + 4, b, std::true_type(), 4);
+    CP_AHEAD16(b, p + 16);
+    body(j, a);
+    CP_AHEAD16(a, p + 32);
+    body(j + 4, b);
   }
   while (j < je) {
     float b[16];
-    CP_LOAD16(b, p + 16);
-    body(j, a, std::false_type(), min(4, je - j));
+    CP_AHEAD16(b, p + 16);
+    if (j + 4 > je) {
+#pragma unroll
+      for (int u = 1; u < 4; u++)
+        if (j + u >= je) {
+          a[4 * u] = a[4 * u + 1] = a[4 * u + 2] = 0.f;
+          a[4 * u + 3] = kFarRec;
+        }
+    }
+    body(j, a);
 #pragma unroll
     for (int t = 0; t < 16; t++) a[t] = b[t];
     j += 4;
@@ -374,6 +400,10 @@ __device__ inline void stream4_f32(const float4 *base, int jb, int je, F &&body)
 // binary64 records only (x, y, z, w), groups of two.
 #define CP_LOAD8D(dst, src)                                                                    \
   _Pragma("unroll") for (int t_ = 0; t_ < 8; t_++) dst[t_] = (src)[t_];
+#define CP_AHEAD8D(dst, src)                                                                   \
+  wait_scalar_loads();                                                                         \
+  CP_LOAD8D(dst, src);                                                                         \
+  __builtin_amdgcn_sched_barrier(0);
 #define CP_REC2D(arr, jj, u) body((jj) + (u), arr[4 * (u)], arr[4 * (u) + 1], arr[4 * (u) + 2], \
                                   arr[4 * (u) + 3])
 template <typename F>
@@ -384,9 +414,9 @@ __device__ inline void stream_f64(const double4 *base, int jb, int je, F &&body)
   CP_LOAD8D(a, p);
   while (j + 4 <= je) {
     double b[8];
-    CP_LOAD8D(b, p + 8);
+    CP_AHEAD8D(b, p + 8);
     CP_REC2D(a, j, 0); CP_REC2D(a, j, 1);
-    CP_LOAD8D(a, p + 16);
+    CP_AHEAD8D(a, p + 16);
     CP_REC2D(b, j + 2, 0); CP_REC2D(b, j + 2, 1);
     j += 4;
     p += 16;
@@ -542,30 +572,22 @@ __device__ inline void loop_xi_f32_few(const PairParams &P, WaveArea A, const La
 #pragma unroll
   for (int k = 0; k < K; k++) n[k] = 0;
   float mn = 3.0e38f;
-  stream4_f32(U.strm, U.jb, U.je, [&](int, const float *q, auto full, int cnt) {
+  stream4_f32(U.strm, U.jb, U.je, [&](int, const float *q) {
 #pragma unroll
     for (int u = 0; u < 4; u += 2) {
-      float d[2 * K];
-      if (!decltype(full)::value && u >= cnt) break;
-      const bool both = decltype(full)::value || u + 1 < cnt;
+      float d[2][K];
 #pragma unroll
       for (int v = 0; v < 2; v++) {
-        if (v && !both) break;
         const float d0 = gram3(rx, ry, rz, b, q[4 * (u + v)], q[4 * (u + v) + 1],
                                q[4 * (u + v) + 2], q[4 * (u + v) + 3]);
 #pragma unroll
         for (int k = 0; k < K; k++) {
-          d[v * K + k] = k ? d0 + c[k] : d0;
-          n[k] += __float_as_uint(d[v * K + k]) >> 31;
+          d[v][k] = k ? d0 + c[k] : d0;
+          n[k] += __float_as_uint(d[v][k]) >> 31;
         }
       }
-      if (both) {
 #pragma unroll
-        for (int k = 0; k < K; k++) mn = fminf(mn, fminf(fabsf(d[2 * k]), fabsf(d[2 * k + 1])));
-      } else {
-#pragma unroll
-        for (int k = 0; k < K; k++) mn = fminf(mn, fabsf(d[k]));
-      }
+      for (int k = 0; k < K; k++) mn = fminf(mn, fminf(fabsf(d[0][k]), fabsf(d[1][k])));
     }
   });
   uint32_t un = 0;
@@ -624,8 +646,7 @@ __device__ inline void loop_xi_f32(const PairParams &P, WaveArea A, const LanePt
   const uint2 *tb = tab32 - P.tab32_lo;
   const float AB = in_vgpr(P.AB32), eps = in_vgpr(P.eps32_3);
   const uint32_t hl = lds_addr(A.hist) + 4u * (uint32_t)(lane & (kXiCols - 1));
-  stream4_f32(U.strm, U.jb, U.je, [&](int j, const float *q, auto full, int cnt) {
-    constexpr bool FULL = decltype(full)::value;
+  stream4_f32(U.strm, U.jb, U.je, [&](int j, const float *q) {
     float v[4], d[4], mn = 3.0e38f;
     uint2 e[4];
     uint32_t flag = 0;
@@ -640,8 +661,8 @@ __device__ inline void loop_xi_f32(const PairParams &P, WaveArea A, const LanePt
       mn = fminf(mn, fabsf(d[u]));
       flag |= e[u].y;
     }
-    if (__builtin_amdgcn_ballot_w64(mn < eps || (int)flag < 0)) {
-      const int n4 = FULL ? 4 : cnt;
+    if (__builtin_amdgcn_ballot_w64(mn < eps) | __builtin_amdgcn_ballot_w64((int)flag < 0)) {
+      const int n4 = min(4, U.je - j);
 #pragma unroll 1
       for (int u = 0; u < n4; u++)
         xi_record<OWN>(P, A, L, lane, rx, ry, rz, ra, U, j + u, tab32, sE, nrechk);
@@ -649,7 +670,6 @@ __device__ inline void loop_xi_f32(const PairParams &P, WaveArea A, const LanePt
     }
 #pragma unroll
     for (int u = 0; u < 4; u++) {
-      if (!FULL && u >= cnt) break;
       if (v[u] < AB && (!OWN || j + u > L.iloc))
         atomicAdd(lds_ptr(lshl_add((uint32_t)((int)__float_as_uint(d[u]) >> 31), 7u, hl + e[u].y)),
                   1u);
@@ -751,7 +771,8 @@ __device__ inline void wp_record(const PairParams &P, WaveArea A, const LanePt &
 // distance of a pi fraction from 1/2 tell with one branch whether any of their
 // pairs is uncertain, and then the four take wp_record.  Bound: VALU issue.
 // Against a decision-table lookup per pair with its compares: w_p of 10^6
-// points 1.88 to 1.74 ms a call, 16 catalogues' w_p and xi 51.0 to 48.5 ms.
+// points 1.88 to 1.63 ms a call, 16 catalogues' w_p and xi 51.0 to 46.1 ms (both
+// with the record groups loaded ahead).
 // exec = valid lanes.
 template <int K, int KX, bool OWN>
 __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt &L, int lane,
@@ -789,9 +810,7 @@ __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt
   uint32_t nx[NX], skip = 0;
 #pragma unroll
   for (int k = 0; k < NX; k++) nx[k] = 0;
-  // rows j .. j + n - 1 (n <= 4; the records past them are loaded but not used)
-  auto rows4 = [&](int j, const float *q, auto full, int n) {
-    constexpr bool FULL = decltype(full)::value;
+  stream4_f32(U.strm, U.jb, U.je, [&](int j, const float *q) {
     float v[4], d[4], dz[4], f[4], s[4], mn = 3.0e38f, mx = 0.f, mnx = 3.0e38f;
     uint32_t m[4], sx[NX], flag = 0;
     uint2 e[4], ex[4];
@@ -823,8 +842,7 @@ __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt
 #pragma unroll
       for (int k = 0; k < KX; k++) {
         const float dk = s[u] + cx[k];
-        const uint32_t g = __float_as_uint(dk) >> 31;
-        sx[k] += FULL || u < n ? g : 0u;
+        sx[k] += __float_as_uint(dk) >> 31;
         mnx = fminf(mnx, fabsf(dk));
       }
       if (XT) {
@@ -834,11 +852,11 @@ __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt
         ex[u].x = __float_as_uint(dk) >> 31;
       }
     }
-    bool unsure = mn < eps || mx > hm;
-    if (KX) unsure = unsure || mnx < epsx;
-    if (TAB) unsure = unsure || (int)flag < 0;
-    if (__builtin_amdgcn_ballot_w64(unsure)) {
-      const int n4 = FULL ? 4 : n;
+    unsigned long long unsure = __builtin_amdgcn_ballot_w64(mn < eps) | __builtin_amdgcn_ballot_w64(mx > hm);
+    if (KX) unsure |= __builtin_amdgcn_ballot_w64(mnx < epsx);
+    if (TAB) unsure |= __builtin_amdgcn_ballot_w64((int)flag < 0);
+    if (unsure) {
+      const int n4 = min(4, U.je - j);
       skip += (uint32_t)n4;
 #pragma unroll 1
       for (int u = 0; u < n4; u++)
@@ -850,7 +868,6 @@ __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt
     for (int k = 0; k < KX; k++) nx[k] += sx[k];
 #pragma unroll
     for (int u = 0; u < 4; u++) {
-      if (!FULL && u >= n) break;
       if ((TAB ? v[u] : d[u]) < top && fabsf(dz[u]) < phi && (!OWN || j + u > jmin)) {
         // the row m edges below the base, pi bin floor(|f|)
         const uint32_t base = TAB ? hi + e[u].y : hi;
@@ -861,8 +878,7 @@ __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt
       if (XT && s[u] < topx && (!OWN || j + u > jmin))
         atomicAdd(lds_ptr(hx + ex[u].y - (ex[u].x << 7)), 1u);
     }
-  };
-  stream4_f32(U.strm, U.jb, U.je, rows4);
+  });
   if (KX > 0) {
     // nx[k]: pairs below xi edge xlo + k
     const uint32_t all = (uint32_t)(U.je - U.jb) - skip;
@@ -1670,18 +1686,20 @@ void k_pairs(PairParams P) {
             const int kw = U.slot_hi - U.slot_lo;
             const int xlo = (sl >> 16) & 255, kx = (int)(((unsigned)sl >> 24) - (unsigned)xlo);
             // xi: no pair below the last edge, one slot (counted at once), up
-            // to three edges, or more
+            // to two edges, or more (chains up to three of either kind were no
+            // faster, and this kernel is already larger than the instruction
+            // cache: 46.0 and 46.1 ms for 16 catalogues)
             const bool sure = !own && !P.noprune, none = sure && xlo > P.nbx;
             const bool once = sure && !none && kx == 0;
             if (once && xlo >= 1 && valid) atomicAdd(&A.histx[xlo * 32 + (lane & 31)], (uint32_t)nj);
             const int kk = none || once ? 0 : kx;
 #define CP_WX(K, KX, O) loop_wp_f32<K, KX, O>(P, A, L, lane, rxf, ryf, rzf, ra, U, xlo, tab32, sE, tabx, sEx, nrechk)
 #define CP_WXK(K) { if (kk == 0) CP_WX(K, 0, false); else if (kk == 1) CP_WX(K, 1, false); \
-                    else if (kk == 2) CP_WX(K, 2, false); else CP_WX(K, 3, false); }
+                    else CP_WX(K, 2, false); }
             if (valid) {
               if (own) CP_WX(0, -1, true);
-              else if (sure && kw <= 3 && U.slot_hi >= 1 && kk <= 3) {
-                if (kw <= 1) CP_WXK(1) else if (kw == 2) CP_WXK(2) else CP_WXK(3)
+              else if (sure && kw <= 2 && U.slot_hi >= 1 && kk <= 2) {
+                if (kw <= 1) CP_WXK(1) else CP_WXK(2)
               } else if (kk == 0 && sure) CP_WX(0, 0, false);
               else CP_WX(0, -1, false);
             }
