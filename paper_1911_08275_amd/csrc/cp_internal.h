@@ -39,7 +39,7 @@ constexpr int kQStride = 512;
 constexpr int kStatWords = 5 + kQueues * kQStride;
 // Most queue items per tile (chunks of the tile's neighbour-column list).
 constexpr int kMaxChunks = 32;
-constexpr int kStaticLds = 256;  // LDS the pair kernel declares statically (queue mask)
+constexpr int kStaticLds = 256;  // LDS the pair kernel declares statically (queue mask, the end of a workgroup)
 constexpr int kWStripe = 8;       // copies of each weight sum per wave (lane & 7)
 
 // Cell counters of the build: one per cell, kCountStride ints apart.

@@ -104,3 +104,29 @@ def test_fused_loops(native, name, refine):
             rw = oracle.wp(c, edges, 6.0, 6, periodic=True, box=box).npairs
             assert (wp[m].reshape(rw.shape) == rw).all(), m
             assert (xi[m] == oracle.xi(c, xe, periodic=True, box=box).npairs).all(), m
+
+
+@pytest.mark.parametrize("mode", ["xi", "wp"])
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 129, 4097, 40_000])
+def test_launch_sizes(native, mode, n):
+    """From one tile to more tiles than waves: workgroups without items, part
+    of their waves with items, items by position and from the queues, the end
+    totals of a workgroup; weighted (sums within 1e-12, the accumulation error
+    of under 2^20 binary64 additions) and not."""
+    rng = np.random.Generator(np.random.PCG64(n))
+    cat = _cloud(n, 60.0, 3)
+    cat = synth.Catalog(cat.x, cat.y, cat.z, rng.uniform(0.5, 1.5, n))
+    edges = np.linspace(0.5, 6.0, 8)
+    d = native.to_device(cat)
+    ref = (oracle.xi(cat, edges, periodic=True, box=60.0) if mode == "xi"
+           else oracle.wp(cat, edges, 6.0, 5, periodic=True, box=60.0))
+    for prec in ("fp64", "fp32"):
+        for ravg in (False, True):
+            _say("launch sizes", mode, n, prec, ravg)
+            opt = dict(precision=prec, periodic=True, boxsize=60.0, refine=(3, 3, 3), need_ravg=ravg)
+            g = (native.countpairs_xi(d, edges, **opt) if mode == "xi"
+                 else native.countpairs_wp(d, edges, 6.0, 5, **opt))
+            assert (g.npairs.reshape(ref.npairs.shape) == ref.npairs).all()
+            if ravg:
+                np.testing.assert_allclose(g.wsum.reshape(ref.wsum.shape), ref.wsum, rtol=1e-12)
+                np.testing.assert_allclose(g.ravg.reshape(ref.ravg.shape), ref.ravg, rtol=1e-12)
