@@ -676,30 +676,35 @@ static int num_cus() {
 // Waves per pair-kernel workgroup: four, or fewer when the per-wave
 // histograms (w_p with many bins, weighted) would not fit the 160 KB of LDS;
 // 0 when not even one wave's fits.
-// Copies of the w_p wave histogram: the tile's points are z-neighbours of
-// one column, so for one streamed point most lanes add to the same few
-// (r_p, pi) counters and their LDS atomics serialise; lane l adds to copy
-// l mod wpc, the copies of a counter in adjacent words.  The most copies
-// (up to 8) that still leave room for five 4-wave workgroups per CU (the
-// pair kernel's register-bound occupancy); CP_WP_COPIES (1, 2, 4 or 8)
-// overrides the choice.
+// Copies of the w_p histogram: the tile's points are z-neighbours of one
+// column, so for one streamed point most lanes add to the same few (r_p, pi)
+// counters and their LDS atomics serialise; lane l adds to copy l mod wpc, the
+// copies of a counter in adjacent words.  Only lanes of one instruction meet, so
+// the waves of a single call's workgroup share one histogram (a batch's waves
+// can be in different catalogues), four of them whatever the tuner says: four times the copies in the same LDS.  Pair
+// kernel of weighted w_p, 250 000 binary64 points: 0.66 ms with one histogram per
+// wave, 0.42 shared; 5 10^4 by 4 10^5 binary32 points 0.62 and 0.36; unweighted
+// w_p of 10^6 points 1.43 and 1.40.  The most copies (up to 32, 8 per wave's own) that still
+// leave room for the workgroups of a CU that the registers allow;
+// CP_WP_COPIES (1, 2, 4 or 8) overrides the choice.
 static int wp_copies(int mode, int prec, int weighted, int n32, int n64, int nb, int npi,
-                     int nx = 0, int nbx = 0) {
+                     int nx = 0, int nbx = 0, bool shared = false) {
   if (mode != WP && mode != WPXI) return 1;
   if (const char *e = getenv("CP_WP_COPIES")) {
     const int c = atoi(e);
     if (c == 1 || c == 2 || c == 4 || c == 8) return c;
   }
-  for (int c = 8; c > 1; c >>= 1) {
+  const size_t budget = (size_t)160 * 1024 / pair_waves(mode, prec, weighted);
+  for (int c = shared ? 32 : 8; c > 1; c >>= 1) {
     const LdsLayout L = lds_layout(mode, prec, weighted, n32, n64, nb, npi, c, nx, nbx);
-    if (L.common + 4 * L.wave_bytes + kStaticLds <= (size_t)160 * 1024 / pair_waves(mode, prec, weighted)) return c;
+    if (L.common + (shared ? 1 : 4) * L.wave_bytes + kStaticLds <= budget) return c;
   }
   return 1;
 }
 
-static int pick_waves(const LdsLayout &LY, size_t *lds, int most = 4) {
+static int pick_waves(const LdsLayout &LY, size_t *lds, int most = 4, bool shared = false) {
   for (int nw = std::min(4, std::max(1, most)); nw >= 1; nw--) {
-    const size_t l = LY.common + (size_t)nw * LY.wave_bytes;
+    const size_t l = LY.common + (size_t)(shared ? 1 : nw) * LY.wave_bytes;
     if (l + kStaticLds <= 160 * 1024) {
       *lds = l;
       return nw;
@@ -1394,10 +1399,17 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg) {
   P.hwr = d_hwr;
   P.stats = d_stats;
   P.hist_stride = nout;
-  P.wpc = wp_copies(c.mode, prec, weighted, n32, n64, nb, npi);
+  P.wpshared = c.mode == WP ? 1 : 0;
+  P.wpc = wp_copies(c.mode, prec, weighted, n32, n64, nb, npi, 0, 0, P.wpshared != 0);
+  // a 32-bit counter must hold what its lanes add between two flushes (2^22
+  // records and a cell each): with under four copies, 256 lanes of a shared one
+  if (P.wpshared && P.wpc < 4 && (c.cross ? c.d2->n : c.d1->n) >= ((int64_t)1 << 23)) {
+    P.wpshared = 0;
+    P.wpc = wp_copies(c.mode, prec, weighted, n32, n64, nb, npi);
+  }
   const LdsLayout LY = lds_layout(c.mode, prec, weighted, n32, n64, nb, npi, P.wpc);
   size_t lds = 0;
-  const int nwaves = pick_waves(LY, &lds, waves_most);
+  const int nwaves = pick_waves(LY, &lds, P.wpshared ? 4 : waves_most, P.wpshared != 0);
   if (!nwaves) return fail(CP_ERR_INVALID_ARG, "too many bins for the LDS budget");
   int grid = 0;
   if ((rc = launch_pairs(st, c.mode, prec, weighted, P, lds, nwaves, &grid))) return rc;

@@ -175,6 +175,7 @@ struct PairParams {
   unsigned long long *hist;  // [nmock][nb * npi]
   double *hw;                // [nmock][nb * npi] sum of weights
   double *hwr;               // [nmock][nb * npi] sum of weight * separation
+  int wpshared;              // w_p: one histogram per workgroup instead of one per wave
   unsigned long long *stats; // kStatWords: candidates, rechecks, cell pairs, pruned,
                              // tile count (written by the pair kernel), queue heads
   int hist_stride;           // nb * npi
@@ -254,8 +255,8 @@ __host__ __device__ constexpr int pair_waves(int mode, int prec, int weighted) {
 // group of four records adds at most 4 x 64.
 constexpr int kListCap = 64 + 4 * 64;
 
-// wpc: copies of the w_p histogram (and weight sums) per wave, interleaved
-// counter by counter; lane l adds to copy l mod wpc.  nx, nbx: the xi table
+// wpc: copies of the w_p histogram (and weight sums) per wave, or per workgroup
+// when its waves share one, interleaved counter by counter; lane l adds to copy l mod wpc.  nx, nbx: the xi table
 // entries and bins of a WPXI launch (xi rows, one per lane pair, follow the
 // w_p histogram).
 __host__ __device__ inline LdsLayout lds_layout(int mode, int prec, int weighted, int n32, int n64,

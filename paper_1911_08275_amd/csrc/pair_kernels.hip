@@ -249,8 +249,8 @@ __device__ inline void flush_xi_rows(uint32_t *rows, unsigned long long *gh, int
     for (int s = 0; s < nb + 2; s++) rows[s * 32 + lane] = 0u;
 }
 
-// The end of a workgroup's waves 0 .. nw - 1, whose areas lie LY.wave_bytes
-// apart from wb: their counters (and weight sums) are added up and go to the
+// The end of a workgroup with nw areas of counters, LY.wave_bytes apart from
+// wb: their counters (and weight sums) are added up and go to the
 // output once per workgroup.  All waves call it, after a barrier.
 template <int MODE, int W>
 __device__ inline void flush_group(const PairParams &P, const LdsLayout &LY, unsigned char *wb,
@@ -323,29 +323,24 @@ __device__ inline void flush_hist(const PairParams &P, WaveArea A, int mock, int
       for (int t = lane; t < 2 * NS * kWStripe; t += 64) A.hw[t] = 0.0;
     }
   } else {
+    // (exchanges: the workgroup's other waves may be adding to a shared
+    // histogram)
     const int npi = P.npi, wpc = P.wpc;
     for (int t = lane; t < nb * npi; t += 64) {
       uint32_t v = 0;
-      for (int c = 0; c < wpc; c++) v += A.hist[(npi + t) * wpc + c];
-      if (v) atomicAdd(gh + t, (unsigned long long)v);
-      if (W) {
-        double a = 0.0, b = 0.0;
-        for (int c = 0; c < wpc; c++) {
-          a += A.hw[2 * ((npi + t) * wpc + c)];
-          b += A.hw[2 * ((npi + t) * wpc + c) + 1];
+      double a = 0.0, b = 0.0;
+      for (int c = 0; c < wpc; c++) {
+        const int i = (npi + t) * wpc + c;
+        v += atomicExch(&A.hist[i], 0u);
+        if (W) {
+          unsigned long long *hw = (unsigned long long *)(A.hw + 2 * i);
+          a += __longlong_as_double((long long)atomicExch(hw, 0ull));
+          b += __longlong_as_double((long long)atomicExch(hw + 1, 0ull));
         }
-        if (a != 0.0) unsafeAtomicAdd(P.hw + (int64_t)mock * P.hist_stride + t, a);
-        if (b != 0.0) unsafeAtomicAdd(P.hwr + (int64_t)mock * P.hist_stride + t, b);
       }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    for (int t = lane; t < NS * npi * wpc; t += 64) {
-      A.hist[t] = 0u;
-      if (W) {
-        A.hw[2 * t] = 0.0;
-        A.hw[2 * t + 1] = 0.0;
-      }
+      if (v) atomicAdd(gh + t, (unsigned long long)v);
+      if (W && a != 0.0) unsafeAtomicAdd(P.hw + (int64_t)mock * P.hist_stride + t, a);
+      if (W && b != 0.0) unsafeAtomicAdd(P.hwr + (int64_t)mock * P.hist_stride + t, b);
     }
     if (MODE == WPXI) flush_xi_rows(A.histx, P.histx + (int64_t)mock * P.histx_stride, P.nbx, lane);
   }
@@ -854,7 +849,7 @@ __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt
   const float topx = XT ? in_vgpr(P.AB32x) : 0.f;
   const uint32_t row4 = (uint32_t)(P.npi * wpc * 4);
   const uint32_t nrow4 = (uint32_t)in_vgpr((int)(0u - row4));
-  const uint32_t lsh = (uint32_t)in_vgpr(wpc == 2 ? 3 : (wpc == 4 ? 4 : (wpc == 8 ? 5 : 2)));
+  const uint32_t lsh = (uint32_t)in_vgpr(2 + __builtin_ctz((unsigned)wpc));
   const uint32_t h0 = lds_addr(A.hist) + 4u * (uint32_t)(lane & (wpc - 1));
   const uint32_t hi = TAB ? h0 : h0 + (uint32_t)U.slot_hi * row4;
   const int lo = in_vgpr(P.tab32_lo), top_ix = in_vgpr(P.tab32_hi), sh = in_vgpr(P.tab_shift);
@@ -1429,7 +1424,9 @@ void k_pairs(PairParams P) {
     }
     for (int t = threadIdx.x; t <= P.nbx; t += blockDim.x) sEx[t] = P.Ex[t];
   }
-  unsigned char *wb = smem + LY.common + (size_t)wid * LY.wave_bytes;
+  const bool shared = MODE == WP && P.wpshared;
+  const int nareas = shared ? 1 : nwaves;
+  unsigned char *wb = smem + LY.common + (size_t)(shared ? 0 : wid) * LY.wave_bytes;
   WaveArea A;
   A.hist = (uint32_t *)wb;
   A.hw = (double *)(wb + LY.wave_hist);
@@ -1441,9 +1438,10 @@ void k_pairs(PairParams P) {
   const int NS = P.nslots;
   const int hwords = MODE == XI ? NS * kXiCols : NS * P.npi * P.wpc;
   const int wwords = MODE == XI ? NS * kWStripe : hwords;
-  for (int t = lane; t < hwords; t += 64) A.hist[t] = 0u;
+  const int z0 = shared ? (int)threadIdx.x : lane, zs = shared ? (int)blockDim.x : 64;
+  for (int t = z0; t < hwords; t += zs) A.hist[t] = 0u;
   if (W) {
-    for (int t = lane; t < wwords; t += 64) {
+    for (int t = z0; t < wwords; t += zs) {
       A.hw[2 * t] = 0.0;
       A.hw[2 * t + 1] = 0.0;
     }
@@ -1456,7 +1454,7 @@ void k_pairs(PairParams P) {
   ItemQueue Q;
   int cur_mock = -1;
   unsigned long long since_flush = 0;
-  const unsigned long long flush_limit = MODE == XI ? (1ull << 30) : (1ull << 24);
+  const unsigned long long flush_limit = MODE == XI ? (1ull << 30) : (1ull << 22);
 
   for (;;) {
     const int64_t tix = Q.next(heads, nitems, &qdrained, lane);
@@ -1844,7 +1842,7 @@ void k_pairs(PairParams P) {
     mock = max(mock, m);
   }
   if (same) {
-    if (mock >= 0) flush_group<MODE, W>(P, LY, smem + LY.common, nwaves, mock);
+    if (mock >= 0) flush_group<MODE, W>(P, LY, smem + LY.common, nareas, mock);
   } else if (cur_mock >= 0) {
     flush_hist<MODE, PREC, W>(P, A, cur_mock, lane);
   }
