@@ -1163,12 +1163,15 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg) {
     PointsDev b = pd[1];
     if (autoc) b.n = 0;
     hipLaunchKernelGGL(k_bbox_partial, dim3(nblk), dim3(256), 0, st, pd[0], b, d_part, d_err0);
-    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(64), 0, st, d_part, nblk, d_part + 6 * nblk);
+    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(256), 0, st, d_part, nblk, d_part + 6 * nblk);
+    // box and error flag lie side by side: one copy
+    unsigned char back[6 * sizeof(double) + sizeof(int)];
     double bb[6];
     int eflag = 0;
-    HIPCHK(hipMemcpyAsync(bb, d_part + 6 * nblk, sizeof(bb), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(&eflag, d_err0, sizeof(int), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(back, d_part + 6 * nblk, sizeof(back), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
+    memcpy(bb, back, sizeof(bb));
+    memcpy(&eflag, back + sizeof(bb), sizeof(int));
     if ((rc = map_err_flags(eflag))) return rc;
     for (int a = 0; a < 3; a++) {
       lo[a] = bb[a];
@@ -1421,16 +1424,25 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg) {
   std::vector<unsigned long long> h;
   std::vector<double> hwv, hwrv;
   if (noalloc) {
-    // straight into the caller's outputs (raw counts and sums, finished
-    // in place below), statistics and error flag on the stack
-    HIPCHK(hipMemcpyAsync(npairs, d_hist, 8 * (size_t)nout, hipMemcpyDeviceToHost, st));
-    if (weighted) {
-      HIPCHK(hipMemcpyAsync(wsum, d_hw, 8 * (size_t)nout, hipMemcpyDeviceToHost, st));
-      HIPCHK(hipMemcpyAsync(ravg, d_hwr, 8 * (size_t)nout, hipMemcpyDeviceToHost, st));
-    }
-    HIPCHK(hipMemcpyAsync(hst, d_stats, sizeof(hst), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(&eflag, d_err, sizeof(int), hipMemcpyDeviceToHost, st));
+    // raw counts and sums into the caller's outputs (finished in place below)
+    // through the stack: the device block is contiguous, and five copies into
+    // pageable memory cost about 12 us each where one does
+    unsigned char back[8 * (3 * kMaxBins + kStatWords) + 8 * 256];
+    const char *dn0 = (const char *)d_hist;
+    const size_t dnn = (size_t)((const char *)(d_err + 1) - dn0);
+    if (dnn > sizeof(back)) return fail(CP_ERR_INTERNAL, "download block larger than expected");
+    HIPCHK(hipMemcpyAsync(back, dn0, dnn, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
+    auto get = [&](void *dst, const void *dev, size_t bytes) {
+      memcpy(dst, back + ((const char *)dev - dn0), bytes);
+    };
+    get(npairs, d_hist, 8 * (size_t)nout);
+    if (weighted) {
+      get(wsum, d_hw, 8 * (size_t)nout);
+      get(ravg, d_hwr, 8 * (size_t)nout);
+    }
+    get(hst, d_stats, sizeof(hst));
+    get(&eflag, d_err, sizeof(int));
   } else {
     // histogram, weight sums, statistics and the error flag are carved
     // consecutively, so one download brings them all

@@ -67,12 +67,27 @@ __global__ __launch_bounds__(256) void k_bbox_partial(PointsDev a, PointsDev b,
   if (threadIdx.x < 6) out[blockIdx.x * 6 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-__global__ __launch_bounds__(64) void k_bbox_final(const double *part, int nblk, double *out) {
-  int k = threadIdx.x;
+// One workgroup folds the partial boxes, a thread per partial: bound by one
+// load latency (one thread per component walking the 256 partials took 40 us).
+__global__ __launch_bounds__(256) void k_bbox_final(const double *part, int nblk, double *out) {
+  __shared__ double red[4][6];
+  double v[6];
+  for (int k = 0; k < 6; k++) v[k] = k < 3 ? DBL_MAX : -DBL_MAX;
+  for (int b = threadIdx.x; b < nblk; b += 256)
+    for (int k = 0; k < 6; k++) v[k] = k < 3 ? fmin(v[k], part[b * 6 + k]) : fmax(v[k], part[b * 6 + k]);
+  for (int k = 0; k < 6; k++) {
+    for (int o = 32; o > 0; o >>= 1) {
+      const double w = __shfl_xor(v[k], o);
+      v[k] = k < 3 ? fmin(v[k], w) : fmax(v[k], w);
+    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][k] = v[k];
+  }
+  __syncthreads();
+  const int k = threadIdx.x;
   if (k >= 6) return;
-  double v = k < 3 ? DBL_MAX : -DBL_MAX;
-  for (int b = 0; b < nblk; b++) v = k < 3 ? fmin(v, part[b * 6 + k]) : fmax(v, part[b * 6 + k]);
-  out[k] = v;
+  double w = red[0][k];
+  for (int r = 1; r < 4; r++) w = k < 3 ? fmin(w, red[r][k]) : fmax(w, red[r][k]);
+  out[k] = w;
 }
 
 // --------------------------------------------------------- fills and scans
