@@ -211,7 +211,7 @@ __host__ __device__ inline int cell_coord(const GridGeom &g, int a, double v) {
 }
 
 // LDS layout of the pair kernel, shared by the host (launch size) and the
-// device: decision tables and squared edges, then per wave the lane-private
+// device: tables and squared edges, then per wave (or per workgroup, w_p) the
 // counters and the weight sums.
 __host__ __device__ inline size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
 
@@ -283,7 +283,7 @@ __host__ __device__ inline LdsLayout lds_layout(int mode, int prec, int weighted
   const int NS = nb + 2;
   const size_t words = mode == XI ? (size_t)NS * kXiCols : (size_t)NS * npi * wpc;
   L.wave_hist = align16(words * 4);
-  // weight sums are shared by the wave (one row of slots), not lane-private
+  // xi weight sums: kWStripe copies per wave
   L.wave_w = weighted ? (mode == XI ? (size_t)NS * kWStripe : words) * 8 : 0;
   L.wave_list = L.wave_hist + 2 * L.wave_w;
   L.wave_histx = L.wave_list + (xi_f32_weighted(mode, prec, weighted) ? (size_t)kListCap * 4 : 0);

@@ -29,11 +29,11 @@
 // the outermost down with vector masks and popcounts; on a 64-wide wave that
 // scan runs about as deep as the innermost bin any lane needs.  Here the
 // unit's separation bounds pick the loop: a unit inside one bin is counted
-// without separations, units spanning two or three slots decide each pair
-// with one or two compares into register counters (and register weight
-// sums), and other units look the bin up in a 2-word LDS table indexed by
-// the exponent and top mantissa bits of the separation, counting into a
-// private row of LDS counters per lane.
+// without separations, units over few edges count the signs of the
+// differences to them (binary64: compares) in registers, with register weight
+// sums, and other units look the pair's edge or bin up in a 2-word LDS table
+// indexed by the exponent and top mantissa bits of the separation, counting
+// into LDS counters, one column per pair of lanes.
 #include "cp_internal.h"
 
 #include <float.h>
