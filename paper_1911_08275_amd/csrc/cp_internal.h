@@ -242,13 +242,16 @@ constexpr int kXiCols = 32;
 // pair kernel at 5 / 6 / 7 waves, in ms: xi of 10^6 and 10^7 binary32 points
 // 9.8 / 8.8 / 8.2 (8: 8.1, but 10^6 points 0.68 to 0.77), weighted xi of 10^6
 // binary64 points 1.49 / 1.46 / 1.48, w_p of 10^6 binary32 points 1.55 / 1.48 /
-// 1.66, fused w_p and xi of 16 catalogues 48.6 / 59.2 / 74.5; the rest the same.
+// 1.66, fused w_p and xi of 16 catalogues 48.6 / 59.2 / 74.5, xi of 10^6 and 10^7
+// binary64 points 18.3 / 16.2 / 14.8 (8: 14.7, but 10^6
+// points 1.01 to 1.04).  The other w_p kernels hold fewer
+// histogram copies in the LDS of more workgroups: weighted, 250 000 binary64
+// points, 0.44 / 0.63.
 // Weighted xi with the binary32 filter holds a pair list per wave and fits
 // four workgroups per CU in LDS.
 __host__ __device__ constexpr int pair_waves(int mode, int prec, int weighted) {
   return xi_f32_weighted(mode, prec, weighted) ? 4
-         : mode == XI && prec == F32R          ? 7
-         : mode == XI && weighted              ? 6
+         : mode == XI                          ? (weighted ? 6 : 7)
          : mode == WP && prec == F32R && !weighted ? 6 : 5;
 }
 // List entries per wave: fewer than 64 are left over after a drain, and a
