@@ -1162,7 +1162,7 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg) {
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, d_err0, (int64_t)1, 0);
     PointsDev b = pd[1];
     if (autoc) b.n = 0;
-    hipLaunchKernelGGL(k_bbox_partial, dim3(nblk), dim3(256), 0, st, pd[0], b, d_part, d_err0);
+    hipLaunchKernelGGL(k_bbox_partial, dim3(nblk), dim3(1024), 0, st, pd[0], b, d_part, d_err0);
     hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(256), 0, st, d_part, nblk, d_part + 6 * nblk);
     // box and error flag lie side by side: one copy
     unsigned char back[6 * sizeof(double) + sizeof(int)];

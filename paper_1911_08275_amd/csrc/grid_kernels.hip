@@ -25,46 +25,58 @@ __device__ inline double load_coord(const void *p, int dtype, int64_t i) {
 // Partial min/max of up to two point sets; out[blk * 6 + {0..5}] =
 // (min x, min y, min z, max x, max y, max z).  Non-finite values set
 // ERRF_NONFINITE and are left out.
-__global__ __launch_bounds__(256) void k_bbox_partial(PointsDev a, PointsDev b,
-                                                      double *out, int *err) {
+// Bound by memory latency: four points in flight per lane (clamped past the
+// end, which repeats a point) and 16 waves a CU; 1.1 10^7 binary32 points took
+// 223 us with one point per lane and four waves, 68 so.
+__global__ __launch_bounds__(1024) void k_bbox_partial(PointsDev a, PointsDev b, double *out,
+                                                       int *err) {
   double mn[3] = {DBL_MAX, DBL_MAX, DBL_MAX};
   double mx[3] = {-DBL_MAX, -DBL_MAX, -DBL_MAX};
   int bad = 0;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int s = 0; s < 2; s++) {
     const PointsDev &P = s ? b : a;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < P.n; i += stride) {
-      double v[3] = {load_coord(P.x, P.dtype, i), load_coord(P.y, P.dtype, i),
-                     load_coord(P.z, P.dtype, i)};
-      bool fin = isfinite(v[0]) && isfinite(v[1]) && isfinite(v[2]);
-      if (P.w) fin = fin && isfinite(P.w[i]);
-      if (!fin) {
-        bad = 1;
-        continue;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < P.n; i += 4 * stride) {
+      double v[4][3], w[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const int64_t j = min(i + u * stride, P.n - 1);
+        v[u][0] = load_coord(P.x, P.dtype, j);
+        v[u][1] = load_coord(P.y, P.dtype, j);
+        v[u][2] = load_coord(P.z, P.dtype, j);
+        w[u] = P.w ? P.w[j] : 1.0;
       }
-      for (int k = 0; k < 3; k++) {
-        mn[k] = fmin(mn[k], v[k]);
-        mx[k] = fmax(mx[k], v[k]);
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        if (!(isfinite(v[u][0]) && isfinite(v[u][1]) && isfinite(v[u][2]) && isfinite(w[u]))) {
+          bad = 1;
+          continue;
+        }
+        for (int k = 0; k < 3; k++) {
+          mn[k] = fmin(mn[k], v[u][k]);
+          mx[k] = fmax(mx[k], v[u][k]);
+        }
       }
     }
   }
   if (bad) atomicOr(err, ERRF_NONFINITE);
-  __shared__ double red[6][256];
+  __shared__ double red[6][16];
   for (int k = 0; k < 3; k++) {
-    red[k][threadIdx.x] = mn[k];
-    red[k + 3][threadIdx.x] = mx[k];
+    for (int o = 32; o > 0; o >>= 1) {
+      mn[k] = fmin(mn[k], __shfl_xor(mn[k], o));
+      mx[k] = fmax(mx[k], __shfl_xor(mx[k], o));
+    }
+    if ((threadIdx.x & 63) == 0) {
+      red[k][threadIdx.x >> 6] = mn[k];
+      red[k + 3][threadIdx.x >> 6] = mx[k];
+    }
   }
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      for (int k = 0; k < 3; k++) {
-        red[k][threadIdx.x] = fmin(red[k][threadIdx.x], red[k][threadIdx.x + w]);
-        red[k + 3][threadIdx.x] = fmax(red[k + 3][threadIdx.x], red[k + 3][threadIdx.x + w]);
-      }
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x < 6) out[blockIdx.x * 6 + threadIdx.x] = red[threadIdx.x][0];
+  const int k = threadIdx.x;
+  if (k >= 6) return;
+  double v = red[k][0];
+  for (int r = 1; r < (int)(blockDim.x >> 6); r++) v = k < 3 ? fmin(v, red[k][r]) : fmax(v, red[k][r]);
+  out[blockIdx.x * 6 + k] = v;
 }
 
 // One workgroup folds the partial boxes, a thread per partial: bound by one

@@ -130,3 +130,27 @@ def test_launch_sizes(native, mode, n):
             if ravg:
                 np.testing.assert_allclose(g.wsum.reshape(ref.wsum.shape), ref.wsum, rtol=1e-12)
                 np.testing.assert_allclose(g.ravg.reshape(ref.ravg.shape), ref.ravg, rtol=1e-12)
+
+
+@pytest.mark.parametrize("n", [1, 63, 1025, 262_145, 1_048_579])
+def test_bounding_box(native, n):
+    """The joint bounding box of a non-periodic call around its loads (a
+    point per thread, four per thread, one more): the last point of either set
+    alone holds an extreme, and its partner sits beside it."""
+    rng = np.random.Generator(np.random.PCG64(n))
+    p = rng.uniform(0.0, 60.0, (n, 3))
+    q = rng.uniform(0.0, 60.0, (9, 3))
+    p[-1] = (200.0, -90.0, 300.0)
+    q[0] = (200.5, -90.25, 300.0)
+    q[-1] = (-150.0, 170.0, -80.0)
+    p[0] = (-150.0, 170.0, -79.5) if n > 1 else p[0]
+    A, B = (synth.Catalog(*(np.ascontiguousarray(v[:, a]) for a in range(3))) for v in (q, p))
+    edges = np.array([0.25, 1.0, 2.0, 4.0])
+    ref = oracle.xi(A, edges, periodic=False, other=B)
+    assert ref.npairs[0] >= (2 if n > 1 else 1)
+    for prec in ("fp64", "fp32"):
+        _say("bounding box", n, prec)
+        for a, b in ((A, B), (B, A)):
+            g = native.countpairs_cross(native.to_device(a), native.to_device(b), edges,
+                                        precision=prec, periodic=False)
+            assert (g.npairs == ref.npairs).all()
