@@ -324,10 +324,10 @@ __device__ inline void flush_hist(const PairParams &P, WaveArea A, int mock, int
     }
   } else {
     // (exchanges: the workgroup's other waves may be adding to a shared
-    // histogram)
+    // histogram; 64 bits: the copies of one counter are what 256 lanes added)
     const int npi = P.npi, wpc = P.wpc;
     for (int t = lane; t < nb * npi; t += 64) {
-      uint32_t v = 0;
+      unsigned long long v = 0;
       double a = 0.0, b = 0.0;
       for (int c = 0; c < wpc; c++) {
         const int i = (npi + t) * wpc + c;
@@ -338,7 +338,7 @@ __device__ inline void flush_hist(const PairParams &P, WaveArea A, int mock, int
           b += __longlong_as_double((long long)atomicExch(hw + 1, 0ull));
         }
       }
-      if (v) atomicAdd(gh + t, (unsigned long long)v);
+      if (v) atomicAdd(gh + t, v);
       if (W && a != 0.0) unsafeAtomicAdd(P.hw + (int64_t)mock * P.hist_stride + t, a);
       if (W && b != 0.0) unsafeAtomicAdd(P.hwr + (int64_t)mock * P.hist_stride + t, b);
     }
