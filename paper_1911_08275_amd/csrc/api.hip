@@ -1404,12 +1404,6 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg) {
   P.hist_stride = nout;
   P.wpshared = c.mode == WP ? 1 : 0;
   P.wpc = wp_copies(c.mode, prec, weighted, n32, n64, nb, npi, 0, 0, P.wpshared != 0);
-  // a 32-bit counter must hold what its lanes add between two flushes (2^22
-  // records and a cell each): with under four copies, 256 lanes of a shared one
-  if (P.wpshared && P.wpc < 4 && (c.cross ? c.d2->n : c.d1->n) >= ((int64_t)1 << 23)) {
-    P.wpshared = 0;
-    P.wpc = wp_copies(c.mode, prec, weighted, n32, n64, nb, npi);
-  }
   const LdsLayout LY = lds_layout(c.mode, prec, weighted, n32, n64, nb, npi, P.wpc);
   size_t lds = 0;
   const int nwaves = pick_waves(LY, &lds, P.wpshared ? 4 : waves_most, P.wpshared != 0);

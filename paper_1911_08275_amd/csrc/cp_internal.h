@@ -15,6 +15,11 @@ constexpr int kMaxBins = 60;        // separation bins; slots 0 and nb+1 are tra
                                     // slot + 1 must fit the 6-bit table code
 constexpr int kMaxPiBins = 256;
 constexpr int kZSortMax = 4096;   // cells up to this many points are z-sorted
+// Records a wave streams between two flushes of its w_p counters, and the most in
+// one unit: a counter holds 32 bits, and one copy takes the pairs of up to 256
+// lanes (one copy of a histogram that four waves share), 2^30 between flushes.
+constexpr int kWpFlush = 1 << 22;
+static_assert(64 * kZSortMax <= kWpFlush, "a run of z-sorted cells is never cut");
 constexpr int kSortWin = 128;     // grouped positions per wave of the z-order pass
 constexpr int kColLds = 8192;     // columns up to which the build groups points through LDS
 constexpr int kColBlocks = 256;   // most blocks of that grouping (matrix of kColBlocks x columns)

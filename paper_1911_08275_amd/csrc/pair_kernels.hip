@@ -1454,7 +1454,7 @@ void k_pairs(PairParams P) {
   ItemQueue Q;
   int cur_mock = -1;
   unsigned long long since_flush = 0;
-  const unsigned long long flush_limit = MODE == XI ? (1ull << 30) : (1ull << 22);
+  const unsigned long long flush_limit = MODE == XI ? (1ull << 30) : (unsigned long long)kWpFlush;
 
   for (;;) {
     const int64_t tix = Q.next(heads, nitems, &qdrained, lane);
@@ -1676,8 +1676,17 @@ void k_pairs(PairParams P) {
         U.je = __builtin_amdgcn_readlane(re, last);
         U.slot_lo = slr & 255;
         U.slot_hi = (slr >> 8) & 255;
+        // w_p: kWpFlush records at a time, so that is the most a lane adds to
+        // a counter between two flushes; the rest comes again as the next unit
+        // (a run's cells are z-sorted and together smaller)
+        const bool cut = MODE != XI && U.je - U.jb > kWpFlush;
+        if (cut) {
+          U.je = U.jb + kWpFlush;
+          if (lane == src) rb = U.je;
+          mk |= 1ull << src;
+        }
         const unsigned long long nj = (unsigned long long)(U.je - U.jb);
-        st_cells += (unsigned long long)nrun;
+        st_cells += cut ? 0ull : (unsigned long long)nrun;
         since_flush += nj;
         if (since_flush > flush_limit) {
           flush_hist<MODE, PREC, W>(P, A, cur_mock, lane);

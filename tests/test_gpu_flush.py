@@ -50,3 +50,19 @@ def test_one_bin_beyond_32_bits(native, prec):
     _say("one bin", prec)
     g = native.countpairs_cross_wp(d1, d2, EDGES, 0.5, 1, precision=prec, refine=(1, 1, 1))
     assert int(g.npairs.sum()) == 256 * (big + nxt)
+
+
+def test_one_copy_beyond_32_bits(native):
+    """256 pi bins and four copies of the histogram: 64 lanes add the records
+    of one cell of more than 2^26 points to the same copy of one counter."""
+    import torch
+    big, nxt = (1 << 26) + (1 << 20), 100
+    d1 = _points(native, 0.0, [(256, 1.0, 1.0)], torch.float32)
+    d2 = _points(native, 1.0, [(big, 0.951, 0.951), (nxt,) + NEXT] + FAR, torch.float32)
+    edges = np.array([0.2, 0.3, 0.4, 0.5, 1.5])
+    _say("one copy", big)
+    g = native.countpairs_cross_wp(d1, d2, edges, 0.5, 256, precision="fp32", refine=(1, 1, 1))
+    dz = 1.0 - float(np.float32(0.951))
+    assert int(g.npairs[3, int(dz / (0.5 / 256))]) == 256 * big
+    assert int(g.npairs.sum()) == 256 * (big + nxt)
+    assert g.stats["cell_pairs"] == 8   # a cut unit counts once
