@@ -130,14 +130,17 @@ typedef struct {
   int precision;             /* CP_PREC_* the pair kernel actually ran.  Binary64
                                 runs whatever was asked for (a) on a grid with a
                                 single wrapped cell on some axis (box under
-                                three cells of reach: per-pair minimum images)
-                                and (b) for weighted xi (need_ravg), where every
+                                three cells of reach: per-pair minimum images),
+                                (b) for weighted xi (need_ravg), where every
                                 counted pair needs its binary64 separation and
-                                the binary64 kernel is faster on gfx950; the
+                                the binary64 kernel is faster on gfx950 (the
                                 environment variable CP_XI_WEIGHTED_BINARY32=1
-                                selects the binary32 screen for (b) instead
-                                (candidates screened in binary32, the surviving
-                                pairs evaluated in binary64: same counts) */
+                                selects the binary32 screen for (b) instead:
+                                candidates screened in binary32, the surviving
+                                pairs evaluated in binary64, same counts) and
+                                (c) where R_max and the cells' sides are above
+                                some 1e17, whose squares come near the largest
+                                binary32 number */
   int tuned;                 /* launch settings: 0 given by the caller (refine
                                 set), 1 tuned during this call, 2 taken from
                                 the tuning cache, 3 library defaults (tuning

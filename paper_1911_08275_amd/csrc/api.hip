@@ -410,19 +410,34 @@ struct Bounds {
   double eta_pi;     // |pi~ - pi| bound (wp)
 };
 
+// Half the diagonal of a cell (w_p: across the line of sight): the longest
+// coordinate vector in a cell's own frame.
+static double cell_radius(int mode, const Geometry &g) {
+  const double z2 = mode == XI ? g.cs[2] * g.cs[2] : 0.0;
+  return 0.5 * std::sqrt(g.cs[0] * g.cs[0] + g.cs[1] * g.cs[1] + z2) * (1 + 1e-6);
+}
+
+// Whether the binary32 loops can hold squares of these lengths.  Their records
+// beyond a unit's last lie at 3.2e38 and stay above every 3e38, and the lanes
+// beyond a tile's last point at 1e18 (its square 2e36) stay beyond E_B, if the
+// squares that a pair within reach forms are below 1e35: lengths of some 1e17.
+// Longer ones run the binary64 kernels.
+static bool f32_range(int mode, const Geometry &g, double EB) {
+  const double G = 2 * cell_radius(mode, g) + std::sqrt(EB);
+  return G * G <= 1e35;
+}
+
 static Bounds error_bounds(int mode, const Geometry &g, double EB, double pimax, double M) {
   const double u = std::ldexp(1.0, -24), u64 = std::ldexp(1.0, -53);
   const double eB = std::sqrt(EB);
   Bounds b;
+  const double P = cell_radius(mode, g);
   if (mode == XI) {
-    const double P =
-        0.5 * std::sqrt(g.cs[0] * g.cs[0] + g.cs[1] * g.cs[1] + g.cs[2] * g.cs[2]) * (1 + 1e-6);
     const double G = 2 * P + eB;
     const double eta = u * G * 1.01 + 4 * std::sqrt(3.0) * u64 * M;
     b.eps = 2.0 * (7.5 * u * G * G + 2 * eB * eta + eta * eta + 8 * u64 * (EB + 2 * eB * M));
     b.eta_pi = 0;
   } else {
-    const double P = 0.5 * std::sqrt(g.cs[0] * g.cs[0] + g.cs[1] * g.cs[1]) * (1 + 1e-6);
     const double G = 2 * P + eB;
     const double eta = u * G * 1.01 + 4 * std::sqrt(2.0) * u64 * M;
     b.eps = 2.0 * (5.5 * u * G * G + 2 * eB * eta + eta * eta + 8 * u64 * (EB + 2 * eB * M));
@@ -1211,6 +1226,7 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg) {
                                refine_eff, ntot);
   int prec = o.precision == CP_PREC_FP32_RECHECK ? F32R : F64;
   if (g.wrap[0] || g.wrap[1] || g.wrap[2]) prec = F64;   // per-pair minimum image: binary64
+  if (!f32_range(c.mode, g, rmax * rmax)) prec = F64;
   // Weighted xi: every counted pair needs its binary64 separation, and on
   // gfx950 the binary64 loops (which skip the square root on records with no
   // lane in range) are faster than the binary32 screen with a list of the
@@ -1761,7 +1777,8 @@ static int batch_prepare(cp_plan &pl, Batch &b, int mode, int prec, const double
   const double lo[3] = {0, 0, 0}, ext[3] = {0, 0, 0};
   b.g = choose_geometry(mode, true, o.boxsize, lo, ext, edges[nedges - 1], pimax, o.refine,
                         pl.maxn);
-  b.prec = (b.g.wrap[0] || b.g.wrap[1] || b.g.wrap[2]) ? F64 : prec;
+  const double R = edges[nedges - 1];
+  b.prec = (b.g.wrap[0] || b.g.wrap[1] || b.g.wrap[2] || !f32_range(mode, b.g, R * R)) ? F64 : prec;
   int rc = make_binning(mode, b.prec, edges, nedges, pimax, b.npi, b.g, o.boxsize, b.B);
   if (rc) return rc;
   b.ncell = (int64_t)b.g.n[0] * b.g.n[1] * b.g.n[2];
