@@ -786,10 +786,10 @@ static int launch_pairs(hipStream_t st, int mode, int prec, int w, const PairPar
 // Whether every item of a finished launch was taken: through the queue heads,
 // or, when there are no more items than waves, one by each wave (ItemQueue).
 static bool drained(const unsigned long long *stats, int64_t nitems, int64_t waves) {
-  if (nitems <= waves) return true;
+  if (nitems <= waves) return stats[5] == (unsigned long long)nitems;
   for (int k = 0; k < kQueues; k++) {
     const int64_t len = nitems * (k + 1) / kQueues - nitems * k / kQueues;
-    if (stats[5 + (size_t)k * kQStride] < (unsigned long long)len) return false;
+    if (stats[kHeads + (size_t)k * kQStride] < (unsigned long long)len) return false;
   }
   return true;
 }

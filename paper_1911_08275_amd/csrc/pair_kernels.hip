@@ -1450,7 +1450,7 @@ void k_pairs(PairParams P) {
 
   unsigned long long st_cand = 0, st_cells = 0, st_pruned = 0;
   uint32_t nrechk = 0;
-  unsigned long long *heads = P.stats + 5;
+  unsigned long long *heads = P.stats + kHeads;
   ItemQueue Q;
   int cur_mock = -1;
   unsigned long long since_flush = 0;
@@ -1855,10 +1855,11 @@ void k_pairs(PairParams P) {
   } else if (cur_mock >= 0) {
     flush_hist<MODE, PREC, W>(P, A, cur_mock, lane);
   }
-  if (threadIdx.x < 4) {
+  const int k = threadIdx.x;
+  if (k < 5) {   // (the sixth word: waves with items; words of one line, one request)
     unsigned long long v = 0;
-    for (int w = 0; w < nwaves; w++) v += end_stat[w][threadIdx.x];
-    if (v) atomicAdd(P.stats + threadIdx.x, v);
+    for (int w = 0; w < nwaves; w++) v += k < 4 ? end_stat[w][k] : end_mock[w] >= 0 ? 1ull : 0ull;
+    if (v) atomicAdd(P.stats + (k < 4 ? k : 5), v);
   }
 }
 

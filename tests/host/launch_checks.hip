@@ -1,0 +1,46 @@
+// Host-side choices and checks around the pair launch, on the CPU: the
+// library's host source is included to reach them.
+#include "../../paper_1911_08275_amd/csrc/api.hip"
+
+#include <cstdio>
+#include <cstdlib>
+
+using namespace cp;
+
+static int g_fail = 0;
+#define CHECK(c)                                                      \
+  do {                                                                \
+    if (!(c)) {                                                       \
+      printf("check failed at line %d: %s\n", __LINE__, #c);          \
+      g_fail = 1;                                                     \
+    }                                                                 \
+  } while (0)
+
+// A launch of no more items than waves that left one out must not pass, nor one
+// with a short queue.
+static void check_drained() {
+  static unsigned long long st[kStatWords];
+  const int64_t waves = 1000;
+  for (int64_t n : {(int64_t)1, (int64_t)7, waves}) {
+    memset(st, 0, sizeof(st));
+    CHECK(!drained(st, n, waves));
+    st[5] = (unsigned long long)n - 1;
+    CHECK(!drained(st, n, waves));
+    st[5] = (unsigned long long)n;
+    CHECK(drained(st, n, waves));
+  }
+  memset(st, 0, sizeof(st));
+  CHECK(drained(st, 0, waves));
+  const int64_t n = waves + 3;
+  for (int k = 0; k < kQueues; k++)
+    st[kStatWords - (kQueues - k) * kQStride] = (unsigned long long)(n * (k + 1) / kQueues - n * k / kQueues);
+  CHECK(drained(st, n, waves));
+  st[kStatWords - kQStride]--;
+  CHECK(!drained(st, n, waves));
+}
+
+int main() {
+  check_drained();
+  if (!g_fail) printf("launch checks passed\n");
+  return g_fail;
+}
