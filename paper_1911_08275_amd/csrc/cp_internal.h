@@ -34,9 +34,8 @@ __host__ __device__ inline int col_blocks(int64_t n) {
 // drains its own queue first, so a cell's records are reused from its XCD's
 // L2, then helps the others.
 constexpr int kQueues = 8;
-// Statistics words: candidates, rechecks, cell pairs, pruned, tile count, waves
-// that had an item (in a launch that takes items by position: the items taken),
-// then from kHeads the kQueues queue heads, kQStride words (4 KB) apart so that their
+// Statistics words: candidates, rechecks, cell pairs, pruned, tile count, items
+// taken by position (launches without queues), then from kHeads the kQueues queue heads, kQStride words (4 KB) apart so that their
 // device-scope atomics land in different memory channels.  Packed into one
 // 64-byte line the heads handed out at most ~86 items per microsecond in all,
 // which bounded launches of many light items (measured: xi at R_max = 10 took
@@ -184,7 +183,7 @@ struct PairParams {
   double *hwr;               // [nmock][nb * npi] sum of weight * separation
   int wpshared;              // w_p: one histogram per workgroup instead of one per wave
   unsigned long long *stats; // kStatWords: candidates, rechecks, cell pairs, pruned,
-                             // tile count (written by the pair kernel), waves with items,
+                             // tile count (written by the pair kernel), items by position,
                              // queue heads
   int hist_stride;           // nb * npi
   // xi of a WPXI launch: few-edge table of s~ = fl32(pi~^2 + rp~^2) (bands

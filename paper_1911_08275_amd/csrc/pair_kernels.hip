@@ -1856,7 +1856,8 @@ void k_pairs(PairParams P) {
     flush_hist<MODE, PREC, W>(P, A, cur_mock, lane);
   }
   const int k = threadIdx.x;
-  if (k < 5) {   // (the sixth word: waves with items; words of one line, one request)
+  // (the sixth word, without queues only: waves with items)
+  if (k < (nitems <= (int64_t)gridDim.x * nwaves ? 5 : 4)) {
     unsigned long long v = 0;
     for (int w = 0; w < nwaves; w++) v += k < 4 ? end_stat[w][k] : end_mock[w] >= 0 ? 1ull : 0ull;
     if (v) atomicAdd(P.stats + (k < 4 ? k : 5), v);
