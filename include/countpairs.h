@@ -90,8 +90,8 @@ typedef struct {
   int refine[3];          /* cells per R_max (pi_max along z for wp) per axis
                              (Section 3.1 bin_refine_factors).  All three 0: the
                              library chooses the refine factors, the queue
-                             items' work-chunk target and the waves per
-                             workgroup by timing candidates on the call's own
+                             items' work-chunk target and (xi, and plans) the
+                             waves per workgroup by timing candidates on the call's own
                              data (best of three whole calls each, coordinate
                              descent), and caches the choice per workload
                              signature (statistic, precision, weights, periodic,

@@ -556,6 +556,9 @@ struct Call {
   // launch settings that refine = 0 leaves to the library (0: defaults)
   int chunk_pct = 0;
   int waves = 0;
+  // w_p with a histogram per wave, as a plan's launch runs it (the trial calls
+  // of a plan's tuning)
+  bool per_wave = false;
 };
 
 static int check_points(const cp_points *p, const char *name) {
@@ -976,8 +979,8 @@ static int map_err_flags(int flags) {
 // whose automatic choice the paper names as future work).  Candidates are
 // timed on the call's own data -- device time of whole calls, best of three --
 // by coordinate descent: the refine factors first, then the work-chunk
-// target of the queue items, then the waves per workgroup; the winner is
-// cached per workload signature (tune_cache.cpp).  CP_AUTOTUNE=0 switches
+// target of the queue items, then the waves per workgroup where they are a
+// choice; the winner is cached per workload signature (tune_cache.cpp).  CP_AUTOTUNE=0 switches
 // tuning off (library defaults).
 
 static const int kRefineCands[][3] = {{2, 2, 2}, {2, 2, 1}, {2, 2, 3}, {3, 3, 2},
@@ -1014,9 +1017,13 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg);
 // Device time of one candidate's settings (refine, chunk target, waves).
 using TuneTimer = std::function<int(const int ref[3], int chunk, int waves, double &ms)>;
 
-// Coordinate descent over the candidates with `time_of` as the objective;
-// stores the best settings under key.
-static int tune_with(const TuneTimer &time_of, const std::string &key, TuneChoice &best) {
+// A single w_p call shares one histogram among four waves whatever is asked for.
+static bool tunes_waves(const Call &c) { return c.mode != WP || c.per_wave; }
+
+// Coordinate descent over the candidates with `time_of` as the objective, over
+// the waves too if they are a choice; stores the best settings under key.
+static int tune_with(const TuneTimer &time_of, const std::string &key, TuneChoice &best,
+                     bool waves) {
   best = TuneChoice();
   best.ms = INFINITY;
   // a candidate that does not fit a caller's workspace is skipped
@@ -1041,8 +1048,9 @@ static int tune_with(const TuneTimer &time_of, const std::string &key, TuneChoic
   for (int ch : kChunkCands)
     if ((rc = consider(bref, ch, 4))) return rc;
   const int bch = best.chunk_pct;
-  for (int wv : kWaveCands)
-    if ((rc = consider(bref, bch, wv))) return rc;
+  if (waves)
+    for (int wv : kWaveCands)
+      if ((rc = consider(bref, bch, wv))) return rc;
   tune_store(key, best);
   return CP_OK;
 }
@@ -1077,7 +1085,9 @@ static int tune(const std::vector<Call> &calls, const std::string &key, TuneChoi
     }
     return CP_OK;
   };
-  return tune_with(time_of, key, best);
+  bool waves = false;
+  for (const Call &c : calls) waves |= tunes_waves(c);
+  return tune_with(time_of, key, best, waves);
 }
 
 // ------------------------------------------------------------- single call
@@ -1418,7 +1428,7 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg) {
   P.hwr = d_hwr;
   P.stats = d_stats;
   P.hist_stride = nout;
-  P.wpshared = c.mode == WP ? 1 : 0;
+  P.wpshared = c.mode == WP && !c.per_wave ? 1 : 0;
   P.wpc = wp_copies(c.mode, prec, weighted, n32, n64, nb, npi, 0, 0, P.wpshared != 0);
   const LdsLayout LY = lds_layout(c.mode, prec, weighted, n32, n64, nb, npi, P.wpc);
   size_t lds = 0;
@@ -2083,7 +2093,9 @@ static int plan_create(const cp_points *mocks, int nmocks, const double *xi_edge
                             xi_edges[xi_nedges - 1] <= wp_edges[wp_nedges - 1] &&
                             xi_edges[xi_nedges - 1] <= pimax;
     // launch settings: the caller's refine, or tuned (cached): by timing
-    // single calls of the requested statistics on the median catalogue, or,
+    // single calls of the requested statistics on the median catalogue (w_p
+    // with the plan's histogram per wave; tuned on a shared one, where waves
+    // are no choice, noise picked two or four of them for the plan), or,
     // for a fused launch, plans of up to four catalogues picked at even
     // quantiles of the pair work (taken as n^2), which the largest dominate
     cp_options po = *o;
@@ -2101,11 +2113,14 @@ static int plan_create(const cp_points *mocks, int nmocks, const double *xi_edge
         std::vector<Call> calls;
         if (xi_edges && !want_fused)
           calls.push_back(Call{XI, false, &mocks[med], nullptr, xi_edges, xi_nedges, 0.0, 1, &po});
-        if (wp_edges)
+        if (wp_edges) {
           calls.push_back(Call{WP, false, &mocks[med], nullptr, wp_edges, wp_nedges, pimax, npibins, &po});
+          calls.back().per_wave = true;
+        }
         const double vol = po.boxsize * po.boxsize * po.boxsize;
         const std::string key = "plan:" + tune_key(calls[0], vol) +
-                                (want_fused ? "+fused" : calls.size() > 1 ? "+wp" : "");
+                                (want_fused ? "+fused" : calls.size() > 1 ? "+wp" : "") +
+                                (wp_edges && !want_fused ? "+waves" : "");
         if (tune_lookup(key, tc)) {
           pl->tuned = 2;
         } else {
@@ -2138,7 +2153,7 @@ static int plan_create(const cp_points *mocks, int nmocks, const double *xi_edge
               cp_plan_destroy(sp);
               return r;
             };
-            rc = tune_with(ptime, key, tc);
+            rc = tune_with(ptime, key, tc, true);
           } else {
             rc = tune(calls, key, tc);
           }

@@ -39,8 +39,34 @@ static void check_drained() {
   CHECK(!drained(st, n, waves));
 }
 
+// Waves are tuned where the launch takes them: not for single w_p calls.
+static void check_tuned_waves() {
+  Call c{};
+  c.mode = WP;
+  CHECK(!tunes_waves(c));
+  c.per_wave = true;
+  CHECK(tunes_waves(c));
+  c.mode = XI;
+  c.per_wave = false;
+  CHECK(tunes_waves(c));
+  for (bool waves : {false, true}) {
+    int calls = 0, two = 0;
+    const TuneTimer t = [&](const int *, int, int wv, double &ms) {
+      calls++;
+      two += wv == 2;
+      ms = wv == 2 ? 1.0 : 2.0;   // two waves look faster
+      return CP_OK;
+    };
+    TuneChoice best;
+    CHECK(tune_with(t, waves ? "with" : "without", best, waves) == CP_OK);
+    CHECK(two == (waves ? 1 : 0) && best.waves == (waves ? 2 : 4));
+    CHECK(calls == 7 + 2 + two);
+  }
+}
+
 int main() {
   check_drained();
+  check_tuned_waves();
   if (!g_fail) printf("launch checks passed\n");
   return g_fail;
 }
