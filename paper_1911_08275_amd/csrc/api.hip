@@ -704,13 +704,13 @@ static int num_cus() {
 // wave, 0.42 shared; 5 10^4 by 4 10^5 binary32 points 0.62 and 0.36; unweighted
 // w_p of 10^6 points 1.43 and 1.40.  The most copies (up to 32, 8 per wave's own) that still
 // leave room for the workgroups of a CU that the registers allow;
-// CP_WP_COPIES (1, 2, 4 or 8) overrides the choice.
+// CP_WP_COPIES (a power of two up to the same most) overrides the choice.
 static int wp_copies(int mode, int prec, int weighted, int n32, int n64, int nb, int npi,
                      int nx = 0, int nbx = 0, bool shared = false) {
   if (mode != WP && mode != WPXI) return 1;
   if (const char *e = getenv("CP_WP_COPIES")) {
     const int c = atoi(e);
-    if (c == 1 || c == 2 || c == 4 || c == 8) return c;
+    if (c >= 1 && c <= (shared ? 32 : 8) && !(c & (c - 1))) return c;
   }
   const size_t budget = (size_t)160 * 1024 / pair_waves(mode, prec, weighted);
   for (int c = shared ? 32 : 8; c > 1; c >>= 1) {

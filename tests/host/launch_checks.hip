@@ -64,8 +64,23 @@ static void check_tuned_waves() {
   }
 }
 
+// Every number of copies that the default may choose can be asked for.
+static void check_copies() {
+  for (bool shared : {false, true})
+    for (int c = 1; c <= 64; c++) {
+      setenv("CP_WP_COPIES", std::to_string(c).c_str(), 1);
+      const int got = wp_copies(WP, F32R, 0, 100, 100, 14, 40, 0, 0, shared);
+      unsetenv("CP_WP_COPIES");
+      const int own = wp_copies(WP, F32R, 0, 100, 100, 14, 40, 0, 0, shared);
+      const bool power = !(c & (c - 1));
+      CHECK(got == (power && c <= (shared ? 32 : 8) ? c : own));
+    }
+  CHECK(wp_copies(WP, F32R, 0, 100, 100, 1, 1, 0, 0, true) == 32);
+}
+
 int main() {
   check_drained();
+  check_copies();
   check_tuned_waves();
   if (!g_fail) printf("launch checks passed\n");
   return g_fail;
