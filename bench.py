@@ -71,16 +71,30 @@ def time_steps(fn, steps, warmup):
 
 
 TRAFFIC_FILES = sorted(glob.glob(os.path.join(ROOT, "profiles", "k_pairs_xi_weighted_1e6_traffic*.md")))
-KERNEL_SRC = os.path.join(ROOT, "paper_1911_08275_amd", "csrc", "pair_kernels.hip")
+KERNEL_FILES = [os.path.join(ROOT, "paper_1911_08275_amd", "csrc", f)
+                for f in ("pair_kernels.hip", "cp_internal.h")]
+
+
+def kernel_build_hash():
+    """What the pair kernels are compiled from: their source, the header that
+    holds their layouts and waves per SIMD, and the compiler flags (register
+    allocation, and with it the spill traffic, follows from all three)."""
+    import hashlib
+    from paper_1911_08275_amd import build
+    h = hashlib.sha256()
+    for path in KERNEL_FILES:
+        with open(path, "rb") as f:
+            h.update(f.read() + b"\0")
+    h.update("\0".join(build.FLAGS).encode())
+    return h.hexdigest()
 
 
 def measured_traffic(refine):
     """HBM bytes per launch of the headline pair kernel from a committed
     FETCH_SIZE / WRITE_SIZE counter summary taken at these refine factors, or
-    None when none matches the kernel source and the refine factors."""
-    import hashlib
+    None when none matches the kernels' build and the refine factors."""
     try:
-        src = hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()
+        src = kernel_build_hash()
     except OSError:
         return None
     want = ",".join(str(r) for r in refine)
@@ -94,7 +108,7 @@ def measured_traffic(refine):
             if line.startswith("- ") and ":" in line:
                 k, v = line[2:].split(":", 1)
                 vals[k.strip()] = v.strip().strip("`")
-        if vals.get("pair_kernels.hip sha256") != src or vals.get("refine") != want:
+        if vals.get("pair kernel build sha256") != src or vals.get("refine") != want:
             continue
         try:
             return int(vals["fetch bytes per launch"]) + int(vals["write bytes per launch"])
