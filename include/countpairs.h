@@ -174,10 +174,10 @@ int countpairs_xi(const cp_points *d, const double *edges, int nedges,
  *   pimax     > 0; 1 <= npibins <= 256 equal pi bins in [0, pimax)
  *   npairs    (nedges-1) * npibins host uint64, rp-major
  *   wsum, rpavg  same shape, when need_ravg
- * Each wave of the pair kernel keeps the whole 2-D histogram in LDS:
+ * The pair kernel keeps the whole 2-D histogram in LDS, one per workgroup (in
+ * plans one per wave, with fewer waves per workgroup as it grows):
  * (nedges + 1) * npibins * 4 bytes, plus 16 bytes per entry when need_ravg,
- * must stay under ~159 KB (fewer waves per workgroup are used as it grows);
- * beyond that the call fails with CP_ERR_INVALID_ARG.
+ * must stay under ~159 KB; beyond that the call fails with CP_ERR_INVALID_ARG.
  */
 int countpairs_wp(const cp_points *d, const double *rp_edges, int nedges,
                   double pimax, int npibins, const cp_options *o,

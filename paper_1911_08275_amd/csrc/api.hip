@@ -691,19 +691,17 @@ static int num_cus() {
   return g_num_cus;
 }
 
-// Waves per pair-kernel workgroup: four, or fewer when the per-wave
-// histograms (w_p with many bins, weighted) would not fit the 160 KB of LDS;
-// 0 when not even one wave's fits.
 // Copies of the w_p histogram: the tile's points are z-neighbours of one
 // column, so for one streamed point most lanes add to the same few (r_p, pi)
 // counters and their LDS atomics serialise; lane l adds to copy l mod wpc, the
 // copies of a counter in adjacent words.  Only lanes of one instruction meet, so
-// the waves of a single call's workgroup share one histogram (a batch's waves
-// can be in different catalogues), four of them whatever the tuner says: four times the copies in the same LDS.  Pair
-// kernel of weighted w_p, 250 000 binary64 points: 0.66 ms with one histogram per
-// wave, 0.42 shared; 5 10^4 by 4 10^5 binary32 points 0.62 and 0.36; unweighted
-// w_p of 10^6 points 1.43 and 1.40.  The most copies (up to 32, 8 per wave's own) that still
-// leave room for the workgroups of a CU that the registers allow;
+// the waves of a single call's workgroup, always four of them, share one
+// histogram (a batch's waves can be in different catalogues): four times the
+// copies in the same LDS.  Pair kernel of weighted w_p, 250 000 binary64 points:
+// 0.66 ms with one histogram per wave, 0.42 shared; 5 10^4 by 4 10^5 binary32
+// points 0.62 and 0.36; unweighted w_p of 10^6 points 1.43 and 1.40.  The most
+// copies (up to 32, 8 in a wave's own) that still leave room for the workgroups
+// of a CU that the registers allow;
 // CP_WP_COPIES (a power of two up to the same most) overrides the choice.
 static int wp_copies(int mode, int prec, int weighted, int n32, int n64, int nb, int npi,
                      int nx = 0, int nbx = 0, bool shared = false) {
@@ -720,6 +718,9 @@ static int wp_copies(int mode, int prec, int weighted, int n32, int n64, int nb,
   return 1;
 }
 
+// Waves per pair-kernel workgroup: the most asked for, or fewer when the
+// per-wave counters (a plan's w_p with many bins) would not fit the 160 KB of
+// LDS; 0 when not even one wave's, or the shared ones, fit.
 static int pick_waves(const LdsLayout &LY, size_t *lds, int most = 4, bool shared = false) {
   for (int nw = std::min(4, std::max(1, most)); nw >= 1; nw--) {
     const size_t l = LY.common + (size_t)(shared ? 1 : nw) * LY.wave_bytes;
@@ -801,7 +802,7 @@ static bool drained(const unsigned long long *stats, int64_t nitems, int64_t wav
 struct Binning {
   EdgeD E;
   EdgeF C32, A32;
-  Table t32, t64, few;   // few: few-edge table over t32's cells (w_p, binary32)
+  Table t32, t64, few;   // few: few-edge table over t32's cells (binary32)
   int shift;
   float AB32;
   float eps32, eps32_3;
@@ -855,9 +856,10 @@ static int make_binning(int mode, int prec, const double *edges, int nedges, dou
     B.inv_dpi32 = (float)(1.0 / B.dpi);
     // pi band, in units of dpi: the estimate's error eta_pi, the roundings of
     // fl32(1 / dpi) and of the product (2u of at most npi + 1), the rounding
-    // of the pre-filter pi_hi32 and of fl32(1 - pi_delta), and the binary64
-    // edges; it also covers pi_max itself, whose edge is the integer npi, so
-    // a pair away from every integer is surely below pi_max
+    // of the pre-filter pi_hi32, those of the test (fl32(1 - pi_delta), u; or
+    // |fl32(fraction - 1/2)| against fl32(1/2 - pi_delta), u / 4 each), and the
+    // binary64 edges; it also covers pi_max itself, whose edge is the integer
+    // npi, so a pair away from every integer is surely below pi_max
     B.pi_delta = (float)(B.bnd.eta_pi / B.dpi + 8 * u * npi + 1e-12 * npi);
     // the binary64 loops bin fl32(|dz|) of the binary64 |dz| < pi_max the
     // same way: its error is at most u |dz| < u pi_max (1.01 for margin)

@@ -170,7 +170,7 @@ struct PairParams {
   // wp
   double pimax, dpi, inv_dpi;   // inv_dpi = fl(1 / dpi)
   int npi;
-  int wpc;                   // copies of the wave's histogram (power of two)
+  int wpc;                   // copies of a wave's or workgroup's histogram (power of two)
   float inv_dpi32, pi_delta, pi_hi32;
   float pi_delta64;          // pi band of the binary64 loops' binary32 pi bin
   // flags
@@ -251,9 +251,10 @@ constexpr int kXiCols = 32;
 // binary64 points 1.49 / 1.46 / 1.48, w_p of 10^6 binary32 points 1.55 / 1.48 /
 // 1.66, fused w_p and xi of 16 catalogues 48.6 / 59.2 / 74.5, xi of 10^6 and 10^7
 // binary64 points 18.3 / 16.2 / 14.8 (8: 14.7, but 10^6
-// points 1.01 to 1.04).  The other w_p kernels hold fewer
-// histogram copies in the LDS of more workgroups: weighted, 250 000 binary64
-// points, 0.44 / 0.63.
+// points 1.01 to 1.04).  The weighted w_p kernels hold fewer histogram copies in
+// the LDS of more workgroups: 250 000 binary64 points 0.44 / 0.63, 5 10^4 by
+// 4 10^5 binary32 points 0.43 / 0.47; unweighted binary64 w_p is as fast with
+// either, 10^6 points 2.05 / 2.05, 250 000 points 0.317 / 0.314.
 // Weighted xi with the binary32 filter holds a pair list per wave and fits
 // four workgroups per CU in LDS.
 __host__ __device__ constexpr int pair_waves(int mode, int prec, int weighted) {

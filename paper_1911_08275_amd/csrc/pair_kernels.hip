@@ -361,9 +361,11 @@ constexpr double kNoPoint = 1e200;   // coordinates of the lanes beyond a tile's
 // each group's loads issued one group ahead.  The main loop handles two
 // groups per trip so the two buffers alternate without copies; the stream
 // arrays are padded by 8 records, so the look-ahead never leaves the
-// allocation.  The remainder goes one record at a time: one more copy of the
-// body instead of eight keeps the kernels small enough for the instruction
-// cache.  The body is called once per record with its values in SGPRs.
+// allocation.  Where the body is called once per record, with its values in
+// SGPRs, the remainder goes one record at a time: one more copy of the body
+// instead of eight keeps the kernels small enough for the instruction cache.
+// Where it is called once per group of four (stream4_f32), the remainder is
+// more groups, the last one filled up.
 
 #define CP_LOAD16(dst, src)                                                                    \
   _Pragma("unroll") for (int t_ = 0; t_ < 16; t_++) dst[t_] = (src)[t_];
@@ -380,9 +382,13 @@ constexpr double kNoPoint = 1e200;   // coordinates of the lanes beyond a tile's
 #define CP_REC4(arr, jj, u) body((jj) + (u), arr[4 * (u)], arr[4 * (u) + 1], arr[4 * (u) + 2], \
                                  arr[4 * (u) + 3])
 
+// Waits for every scalar load and LDS operation issued so far (s_waitcnt
+// lgkmcnt(0)); the second form also keeps the compiler from moving anything
+// across it.
+__device__ inline void wait_lgkm() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 __device__ inline void wait_scalar_loads() {
   __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+  wait_lgkm();
   __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -729,15 +735,16 @@ __device__ inline void loop_xi_f32(const PairParams &P, WaveArea A, const LanePt
 }
 
 // wp, binary32 filter (the loops below): the r_p^2 estimate v~ (Gram form in
-// the streamed cell's frame) goes through the decision table, the line of
-// sight pi~ = |qz - rz| (cell-local coordinates) is binned by multiplying
-// with 1/dpi, and a pair is in range when v~ < AB32 and pi~ < pi_hi32 (not
-// surely beyond r_p,max or pi_max); it is uncertain when v~ lies in an edge's
-// band or when the fraction of f = pi~ / dpi lies within pi_delta of an
-// integer.  pi_max is the edge at the integer npi and the band covers the
-// pre-filter's slack, so a certain pair is below pi_max and its bin floor(f)
-// is at most npi - 1.  v~ < AB32 keeps the table index at or below the
-// table's top, so the index is clamped below only.
+// the streamed cell's frame) is set against the edges, by differences
+// (unweighted) or a decision table (weighted), the line of sight pi~ =
+// |qz - rz| (cell-local coordinates) is binned by multiplying with 1/dpi, and a
+// pair is in range when v~ < AB32 and pi~ < pi_hi32 (not surely beyond r_p,max
+// or pi_max); it is uncertain when v~ lies in an edge's band or when the
+// fraction of f = pi~ / dpi lies within pi_delta of an integer.  pi_max is the
+// edge at the integer npi and the band covers the pre-filter's slack, so a
+// certain pair is below pi_max and its bin floor(f) is at most npi - 1.  The
+// weighted loop tests v~ < AB32 before its table lookup, which keeps the index at
+// or below the table's top: it is clamped below only.
 
 // Binary64 re-evaluation of one uncertain wp pair (unweighted).  Catalogues on a
 // lattice put a third of their pairs on bin edges, so the slot is scanned from
@@ -996,13 +1003,6 @@ __device__ inline void loop_wp_f32_w(const PairParams &P, WaveArea A, const Lane
            });
 }
 
-// Waits for every scalar load and LDS operation issued so far (s_waitcnt
-// lgkmcnt(0)).  Scalar loads complete out of order, so before a group of
-// streamed records is used the compiler waits for all of them; issuing the
-// look-ahead load of the next group only after this wait lets it overlap the
-// work on the current group.
-__device__ inline void wait_lgkm() { __builtin_amdgcn_s_waitcnt(0xC07F); }
-
 // Weighted xi, binary32 filter with compaction, for units whose separation
 // range reaches E_B (or lies below E_0).  The weighted mean needs the
 // binary64 separation of every counted pair.  Evaluated for every candidate
@@ -1134,6 +1134,8 @@ __device__ inline void loop_xi_f32_w(const PairParams &P, WaveArea A, int lane, 
   sfloat *p = (sfloat *)(U.strm + U.jb);
   float a[16];
   CP_LOAD16(a, p);
+  // (scalar loads complete out of order, so the wait before a group's use is a
+  // wait for all; the next group's load goes out after it)
   for (int jr = 0; jr < nrec; jr += 4) {
     wait_lgkm();
     service();
