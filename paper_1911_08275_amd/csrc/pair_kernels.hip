@@ -99,6 +99,18 @@ __device__ inline int exact_slot_top(const double *E, int nb, double s) {
   return k;
 }
 
+// The same by halving, at most six dependent reads: for the re-evaluations, whose
+// pairs may lie anywhere.
+__device__ inline int exact_slot_bisect(const double *E, int nb, double s) {
+  int lo = 0, hi = nb + 1;   // edges [0, lo) are at or below s, [hi, nb] above
+  while (lo < hi) {
+    const int m = (lo + hi) >> 1;
+    if (E[m] <= s) lo = m + 1;
+    else hi = m;
+  }
+  return lo;
+}
+
 // Pi bin of a binary64 |dz| < pi_max: l with q_l <= pi < q_{l+1},
 // q_l = fl(l * dpi).  The product with fl(1 / dpi) lands within one of l
 // (|dz| / dpi < 257 and both roundings are relative), so one compare each
@@ -746,12 +758,12 @@ __device__ inline void loop_xi_f32(const PairParams &P, WaveArea A, const LanePt
 // weighted loop tests v~ < AB32 before its table lookup, which keeps the index at
 // or below the table's top: it is clamped below only.
 
-// Binary64 re-evaluation of one uncertain wp pair (unweighted).  Catalogues on a
-// lattice put a third of their pairs on bin edges, so the slot is scanned from
-// the outermost edge, where most pairs lie: 10^6 lattice points, 14 log bins,
-// 40 unit pi bins, pair kernel 9.4 (from the innermost edge) to 5.6 ms, four such
-// catalogues' w_p and xi 41.5 to 26.8 (8.2 and 34.1 with one decision-table
-// lookup per pair, which re-evaluated from the innermost edge too).
+// Binary64 re-evaluation of one uncertain wp pair (unweighted).  Where many pairs
+// are uncertain the search for the slot is most of the time: pair kernel of 10^6
+// lattice points (a third of the pairs on an edge), 14 log bins and 40 unit pi
+// bins, scanned from the innermost edge 9.3 ms, from the outermost 5.6, halved
+// 5.1, and four such catalogues' w_p and xi 41.9, 26.8 and 25.1; 8 10^5 clustered
+// points, 60 bins of r_p 2.9 to 4.2 (two edges to a table cell) 2.8, 8.9 and 2.2.
 template <bool SHIFT>
 __device__ inline void recheck_wp(const PairParams &P, WaveArea A, const LanePt &L, const Unit &U,
                                   int j, const double *sE, int cpy) {
@@ -763,7 +775,7 @@ __device__ inline void recheck_wp(const PairParams &P, WaveArea A, const LanePt 
   const double rp2 = dx * dx + dy * dy;
   const double pz64 = fabs(dz);
   if (pz64 < P.pimax && rp2 < P.EB)
-    atomicAdd(&A.hist[(exact_slot_top(sE, P.nb, rp2) * P.npi +
+    atomicAdd(&A.hist[(exact_slot_bisect(sE, P.nb, rp2) * P.npi +
                        exact_pibin(pz64, P.dpi, P.inv_dpi, P.npi)) * P.wpc + cpy], 1u);
 }
 
@@ -816,7 +828,7 @@ __device__ inline void wp_record(const PairParams &P, WaveArea A, const LanePt &
         double dx, dy, dz;
         ref_sep<true, false>(L.x, L.y, L.z, DP[4 * j], DP[4 * j + 1], DP[4 * j + 2], U.S, wz, 0.0,
                              0.0, dx, dy, dz);
-        at = exact_slot_top(sEx, P.nbx, (dx * dx + dy * dy) + dz * dz) * 128;
+        at = exact_slot_bisect(sEx, P.nbx, (dx * dx + dy * dy) + dz * dz) * 128;
         nrechk++;
       }
       atomicAdd(lds_ptr(lds_addr(A.histx) + (uint32_t)(at + (lane & 31) * 4)), 1u);
