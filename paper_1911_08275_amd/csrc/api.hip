@@ -788,9 +788,9 @@ static int launch_pairs(hipStream_t st, int mode, int prec, int w, const PairPar
 }
 
 // Whether every item of a finished launch was taken: through the queue heads,
-// or, when there are no more items than waves, one by each wave (ItemQueue).
-static bool drained(const unsigned long long *stats, int64_t nitems, int64_t waves) {
-  if (nitems <= waves) return stats[5] == (unsigned long long)nitems;
+// or, in a launch without queues (position_items), one by each wave.
+static bool drained(const unsigned long long *stats, int64_t nitems, int64_t by_position) {
+  if (nitems <= by_position) return stats[5] == (unsigned long long)nitems;
   for (int k = 0; k < kQueues; k++) {
     const int64_t len = nitems * (k + 1) / kQueues - nitems * k / kQueues;
     if (stats[kHeads + (size_t)k * kQStride] < (unsigned long long)len) return false;
@@ -1391,6 +1391,7 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg) {
   split_columns(g, autoc, rmax, c.mode == XI ? rmax : c.pimax, (double)p2.n,
                 (prec == F64 ? 2.0 : 1.0) * (weighted ? 2.0 : 1.0) * (c.mode == WP ? 2.5 : 1.0),
                 chunk_pct, P);
+  P.shares = position_shares(p2.n, prec == F32R && !weighted ? sizeof(float4) : sizeof(double4));
   P.geom1 = &d_sm->geom[0];
   P.geom2 = &d_sm->geom[1];
   P.pos1 = S1.pos;
@@ -1499,7 +1500,7 @@ static int run(const Call &c, uint64_t *npairs, double *wsum, double *ravg) {
   const int ntiles = (int)hst[4];
   rc = map_err_flags(eflag);
   if (!rc) {
-    if (!drained(hst, (int64_t)ntiles * P.nsplit, (int64_t)grid * nwaves))
+    if (!drained(hst, (int64_t)ntiles * P.nsplit, position_items(grid, nwaves)))
       rc = fail(CP_ERR_INTERNAL, "work queue not drained");
   }
   if (rc) {
@@ -1903,6 +1904,7 @@ static int batch_upload(cp_plan &pl, Batch &b) {
   split_columns(b.g, true, std::sqrt(b.B.E[b.nb]), b.mode == XI ? std::sqrt(b.B.E[b.nb]) : b.pimax,
                 (double)b.npts_tot / std::max(1, pl.nmock),
                 (b.prec == F64 ? 2.0 : 1.0) * (b.mode == WP ? 2.5 : 1.0), b.chunk_pct, P);
+  P.shares = position_shares(b.npts_tot, b.prec == F32R ? sizeof(float4) : sizeof(double4));
   P.geom1 = b.d_geom;
   P.geom2 = b.d_geom;
   P.pos1 = b.S.pos;
@@ -2319,7 +2321,7 @@ int cp_plan_results(cp_plan *pl, uint64_t *xi_npairs, uint64_t *wp_npairs) {
       std::vector<unsigned long long> st(kStatWords);
       HIPCHK(hipMemcpy(st.data(), b.d_stats, sizeof(unsigned long long) * kStatWords,
                        hipMemcpyDeviceToHost));
-      if (!drained(st.data(), (int64_t)st[4] * b.P.nsplit, (int64_t)b.grid * b.nwaves))
+      if (!drained(st.data(), (int64_t)st[4] * b.P.nsplit, position_items(b.grid, b.nwaves)))
         return fail(CP_ERR_INTERNAL, "work queue not drained");
     }
     if (!out) continue;

@@ -43,6 +43,32 @@ constexpr int kQueues = 8;
 constexpr int kQStride = 512;
 constexpr int kHeads = 6;
 constexpr int kStatWords = kHeads + kQueues * kQStride;
+// Items by position: a launch with no more items than waves takes them without the
+// queues, a run of nwaves items per workgroup (ItemQueue).  The most items of
+// such a launch, and workgroup b's run [begin, end), empty at the end: runs in
+// order, or (share) each XCD's in its own contiguous share, which its
+// waves hold because the grid is a multiple of the XCDs.
+__host__ __device__ inline int64_t position_items(int64_t grid, int nwaves) {
+  return grid % kQueues ? 0 : grid * nwaves;
+}
+struct ItemRun {
+  int64_t begin, end;
+};
+__host__ __device__ inline ItemRun position_run(int64_t nitems, int64_t b, int nwaves, bool share) {
+  const int64_t k = b % kQueues;
+  ItemRun r{b * nwaves, nitems};
+  if (share) r = {nitems * k / kQueues + b / kQueues * nwaves, nitems * (k + 1) / kQueues};
+  if (r.end > r.begin + nwaves) r.end = r.begin + nwaves;
+  return r;
+}
+// Which of the two: in order the XCDs' loads are even where the points are not,
+// but each XCD reads all of the searched records; beyond its 4 MB of L2 the
+// shares are faster.  Pair kernel in order / in shares: xi of 10^4 by 2.35 10^5
+// binary64 points (7.5 MB) 2.8 / 2.3 ms, 2 10^4 by 10^6 0.22 / 0.17; 5 10^3 by 2.35
+// 10^5 binary32 points in clusters (3.8 MB) 0.73 / 0.85, 3 10^4 points 0.13 / 0.13.
+__host__ __device__ inline bool position_shares(int64_t records, int bytes) {
+  return records * bytes > (4 << 20);
+}
 // Most queue items per tile (chunks of the tile's neighbour-column list).
 constexpr int kMaxChunks = 32;
 constexpr int kStaticLds = 256;  // LDS the pair kernel declares statically (queue mask, the end of a workgroup)
@@ -142,6 +168,7 @@ struct PairParams {
   const Tile *tiles;
   const int *ntiles;         // device: number of tiles in the queue
   int nsplit;                // queue items per tile: chunks of its neighbour-column list
+  int shares;                // items by position: in shares of the XCDs (position_run)
   int chunk[kMaxChunks + 1]; // chunk k covers list columns [chunk[k], chunk[k + 1])
   // geometry (indexed by tile.mock); set 2 is the searched (streamed) set
   const GridGeom *geom1;

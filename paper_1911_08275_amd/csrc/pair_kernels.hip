@@ -1359,10 +1359,11 @@ __device__ inline void loop_f64(const PairParams &P, WaveArea A, const LanePt &L
 // wave otherwise tried all eight heads, and those atomics queued at the memory
 // side with other waves' misses behind them.
 //
-// A launch with no more items than waves makes no atomic at all, the w-th wave
-// takes the w-th item: an atomic on a head that other XCDs use too takes about
-// 64 ns of its word's time, and with one per item and a failing one per
-// workgroup and queue a launch of 1 105 items took 86 us (38 with fixed items).
+// A launch with no more items than waves makes no atomic at all, every wave
+// takes the item of its position (position_run): an atomic on a head that other
+// XCDs use too takes about 64 ns of its word's time, and with one per item and a
+// failing one per workgroup and queue a launch of 1 105 items took 86 us (38 with
+// fixed items).
 // Above that the heads balance the load, which fixed first items did not
 // improve (xi at R_max 80: 6.9 and 7.1 ms).
 struct ItemQueue {
@@ -1370,13 +1371,15 @@ struct ItemQueue {
   bool first = true;
 
   // The wave's next item, -1 when there is none.
-  __device__ inline int64_t next(unsigned long long *heads, int64_t nitems, uint32_t *qdrained,
-                                 int lane) {
-    if (nitems <= (int64_t)gridDim.x * (blockDim.x >> 6)) {
-      const int64_t w = uni64((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+  __device__ inline int64_t next(unsigned long long *heads, int64_t nitems, bool shares,
+                                 uint32_t *qdrained, int lane) {
+    const int nw = (int)(blockDim.x >> 6);
+    if (nitems <= position_items(gridDim.x, nw)) {
+      const ItemRun R = position_run(nitems, blockIdx.x, nw, shares);
+      const int64_t w = uni64(R.begin + (threadIdx.x >> 6));
       const bool f = first;
       first = false;
-      return f && w < nitems ? w : -1;
+      return f && w < R.end ? w : -1;
     }
     const int home = (int)(blockIdx.x % kQueues);
     int64_t tix = -1;
@@ -1414,7 +1417,11 @@ void k_pairs(PairParams P) {
   if (blockIdx.x == 0 && threadIdx.x == 0) P.stats[4] = (unsigned long long)ntiles;
   // a workgroup without items (ItemQueue)
   const int nwaves = (int)(blockDim.x >> 6);
-  if (nitems <= (int64_t)gridDim.x * nwaves && (int64_t)blockIdx.x * nwaves >= nitems) return;
+  const bool by_position = nitems <= position_items(gridDim.x, nwaves);
+  if (by_position) {
+    const ItemRun R = position_run(nitems, blockIdx.x, nwaves, P.shares != 0);
+    if (R.begin >= R.end) return;
+  }
   if (threadIdx.x == 0) qdrained = 0u;
   const int lane = threadIdx.x & 63;
   const int wid = threadIdx.x >> 6;
@@ -1476,7 +1483,7 @@ void k_pairs(PairParams P) {
   const unsigned long long flush_limit = MODE == XI ? (1ull << 30) : (unsigned long long)kWpFlush;
 
   for (;;) {
-    const int64_t tix = Q.next(heads, nitems, &qdrained, lane);
+    const int64_t tix = Q.next(heads, nitems, P.shares != 0, &qdrained, lane);
     if (tix < 0) break;
     // item = (tile, chunk of its neighbour columns): consecutive items share
     // a tile, so its chunks run on different waves at the same time
@@ -1876,7 +1883,7 @@ void k_pairs(PairParams P) {
   }
   const int k = threadIdx.x;
   // (the sixth word, without queues only: waves with items)
-  if (k < (nitems <= (int64_t)gridDim.x * nwaves ? 5 : 4)) {
+  if (k < (by_position ? 5 : 4)) {
     unsigned long long v = 0;
     for (int w = 0; w < nwaves; w++) v += k < 4 ? end_stat[w][k] : end_mock[w] >= 0 ? 1ull : 0ull;
     if (v) atomicAdd(P.stats + (k < 4 ? k : 5), v);

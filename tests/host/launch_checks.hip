@@ -78,7 +78,28 @@ static void check_copies() {
   CHECK(wp_copies(WP, F32R, 0, 100, 100, 1, 1, 0, 0, true) == 32);
 }
 
+// By position every item goes to one wave, in order and in shares.
+static void check_positions() {
+  for (int64_t grid : {8, 256, 1280, 1792})
+    for (int nw = 1; nw <= 4; nw++)
+      for (bool share : {false, true}) {
+        const int64_t most = position_items(grid, nw);
+        for (int64_t n : {(int64_t)1, (int64_t)2, (int64_t)7, (int64_t)65, most / 3, most - 1, most}) {
+          if (n < 1 || n > most) continue;
+          std::vector<int> got(n, 0);
+          for (int64_t b = 0; b < grid; b++) {
+            const ItemRun r = position_run(n, b, nw, share);
+            CHECK(r.end <= r.begin + nw && r.end <= n);
+            for (int64_t i = r.begin; i < r.end; i++) got[i]++;
+          }
+          CHECK(std::count(got.begin(), got.end(), 1) == n);
+        }
+      }
+  CHECK(position_items(12, 4) == 0);
+}
+
 int main() {
+  check_positions();
   check_drained();
   check_copies();
   check_tuned_waves();
