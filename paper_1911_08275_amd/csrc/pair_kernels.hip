@@ -797,11 +797,11 @@ __device__ inline void recheck_wp(const PairParams &P, WaveArea A, const LanePt 
 template <bool XIDEC>
 __device__ inline void wp_record(const PairParams &P, WaveArea A, const LanePt &L, int jmin,
                                  int lane, float rx, float ry, float rz, float ra, const Unit &U,
-                                 int j, const uint2 *tab32, const double *sE, const uint2 *tabx,
+                                 int j, float q0, float q1, float q2, float q3,
+                                 const uint2 *tab32, const double *sE, const uint2 *tabx,
                                  const double *sEx, uint32_t &nrechk) {
-  sfloat *q = (sfloat *)(U.strm + j);
-  const float v = __builtin_fmaf(ry, q[1], __builtin_fmaf(rx, q[0], ra)) + q[3];
-  const float pz = fabsf(q[2] - rz);
+  const float v = __builtin_fmaf(ry, q1, __builtin_fmaf(rx, q0, ra)) + q3;
+  const float pz = fabsf(q2 - rz);
   const int cpy = lane & (P.wpc - 1), row4 = P.npi * P.wpc * 4;
   const bool ok = j > jmin;
   if (ok && v < P.AB32 && pz < P.pi_hi32) {
@@ -833,6 +833,37 @@ __device__ inline void wp_record(const PairParams &P, WaveArea A, const LanePt &
       }
       atomicAdd(lds_ptr(lds_addr(A.histx) + (uint32_t)(at + (lane & 31) * 4)), 1u);
     }
+  }
+}
+
+// A unit of under kFewRecs records: one by one through wp_record, each loaded
+// ahead, with nothing to set up and no group to fill up (bound by latency; units
+// of a few records are what sparse catalogues have).  Pair kernel of w_p of 5.5
+// 10^5 points with 4 in reach of each 2.35 ms in groups, 1.85 one by one; w_p and xi
+// of catalogues like it 8.9 and 6.3.  2, 4, 8 and 16 records as the limit: 1.88,
+// 1.83, 1.82 and 1.83.
+constexpr int kFewRecs = 8;
+template <bool XIDEC>
+__device__ inline void loop_wp_single(const PairParams &P, WaveArea A, const LanePt &L, int jmin,
+                                      int lane, float rx, float ry, float rz, float ra,
+                                      const Unit &U, const uint2 *tab32, const double *sE,
+                                      const uint2 *tabx, const double *sEx, uint32_t &nrechk) {
+  sfloat *p = (sfloat *)(U.strm + U.jb);
+  float a[4];
+#pragma unroll
+  for (int t = 0; t < 4; t++) a[t] = p[t];
+#pragma unroll 1
+  for (int j = U.jb; j < U.je; j++) {
+    p += 4;
+    float b[4];
+    wait_scalar_loads();
+#pragma unroll
+    for (int t = 0; t < 4; t++) b[t] = p[t];
+    __builtin_amdgcn_sched_barrier(0);
+    wp_record<XIDEC>(P, A, L, jmin, lane, rx, ry, rz, ra, U, j, a[0], a[1], a[2], a[3], tab32, sE,
+                     tabx, sEx, nrechk);
+#pragma unroll
+    for (int t = 0; t < 4; t++) a[t] = b[t];
   }
 }
 
@@ -934,9 +965,11 @@ __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt
       const int n4 = min(4, U.je - j);
       skip += (uint32_t)n4;
 #pragma unroll 1
-      for (int u = 0; u < n4; u++)
-        wp_record<KX != 0>(P, A, L, jmin, lane, rx, ry, rz, ra, U, j + u, tab32, sE, tabx, sEx,
-                           nrechk);
+      for (int u = 0; u < n4; u++) {
+        sfloat *r = (sfloat *)(U.strm + (j + u));
+        wp_record<KX != 0>(P, A, L, jmin, lane, rx, ry, rz, ra, U, j + u, r[0], r[1], r[2], r[3],
+                           tab32, sE, tabx, sEx, nrechk);
+      }
       return;
     }
 #pragma unroll
@@ -1784,14 +1817,17 @@ void k_pairs(PairParams P) {
             // faster, and this kernel is already larger than the instruction
             // cache: 46.0 and 46.1 ms for 16 catalogues)
             const bool sure = !own && !P.noprune, none = sure && xlo > P.nbx;
-            const bool once = sure && !none && kx == 0;
+            const bool few = nj < kFewRecs;
+            const bool once = sure && !none && kx == 0 && !few;
             if (once && xlo >= 1 && valid) atomicAdd(&A.histx[xlo * 32 + (lane & 31)], (uint32_t)nj);
             const int kk = none || once ? 0 : kx;
+#define CP_FEW(X) loop_wp_single<X>(P, A, L, own ? L.iloc : -1, lane, rxf, ryf, rzf, ra, U, tab32, sE, tabx, sEx, nrechk)
 #define CP_WX(K, KX, O) loop_wp_f32<K, KX, O>(P, A, L, lane, rxf, ryf, rzf, ra, U, xlo, tab32, sE, tabx, sEx, nrechk)
 #define CP_WXK(K) { if (kk == 0) CP_WX(K, 0, false); else if (kk == 1) CP_WX(K, 1, false); \
                     else CP_WX(K, 2, false); }
             if (valid) {
-              if (own) CP_WX(0, -1, true);
+              if (few) CP_FEW(true);
+              else if (own) CP_WX(0, -1, true);
               else if (sure && kw <= 2 && U.slot_hi >= 1 && kk <= 2) {
                 if (kw <= 1) CP_WXK(1) else CP_WXK(2)
               } else if (kk == 0 && sure) CP_WX(0, 0, false);
@@ -1804,13 +1840,15 @@ void k_pairs(PairParams P) {
             const int kw = U.slot_hi - U.slot_lo;
 #define CP_WF(K, O) loop_wp_f32<K, 0, O>(P, A, L, lane, rxf, ryf, rzf, ra, U, 0, tab32, sE, tabx, sEx, nrechk)
             if (valid) {
-              if (own) CP_WF(0, true);
+              if (nj < kFewRecs) CP_FEW(false);
+              else if (own) CP_WF(0, true);
               else if (kw > 3 || P.noprune || U.slot_hi < 1) CP_WF(0, false);
               else if (kw <= 1) CP_WF(1, false);
               else if (kw == 2) CP_WF(2, false);
               else CP_WF(3, false);
             }
 #undef CP_WF
+#undef CP_FEW
           } else {
             // weighted: every in-range pair takes the binary64 separation,
             // where the shift costs an add per axis
