@@ -929,7 +929,15 @@ __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt
       dz[u] = q[4 * u + 2] - rz;
       f[u] = dz[u] * inv;
       if (KX) s[u] = __builtin_fmaf(dz[u], dz[u], v[u]);
-      if (XT) ex[u] = tbx[min(max(__float_as_int(s[u]) >> shx, lox), topx_ix)];
+    }
+    // (xi reaches less far along z than w_p, and the records come in z order: w_p
+    // and xi of 5 10^5 points in cells of R_max 2.74 ms without this test, 2.60 with)
+    bool anyx = false;
+    if (XT) {
+      anyx = __builtin_amdgcn_ballot_w64(fminf(fminf(s[0], s[1]), fminf(s[2], s[3])) < topx) != 0;
+      if (anyx)
+#pragma unroll
+        for (int u = 0; u < 4; u++) ex[u] = tbx[min(max(__float_as_int(s[u]) >> shx, lox), topx_ix)];
     }
 #pragma unroll
     for (int u = 0; u < 4; u++) {
@@ -951,7 +959,10 @@ __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt
         sx[k] += __float_as_uint(dk) >> 31;
         mnx = fminf(mnx, fabsf(dk));
       }
-      if (XT) {
+    }
+    if (XT && anyx) {
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
         const float dk = s[u] - __uint_as_float(ex[u].x);
         mnx = fminf(mnx, fabsf(dk));
         flag |= ex[u].y;
@@ -983,8 +994,12 @@ __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt
         asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(x) : "v"(m[u]), "v"(nrow4), "v"(base));
         atomicAdd(lds_ptr(lshl_add((uint32_t)fabsf(f[u]), lsh, x)), 1u);
       }
-      if (XT && s[u] < topx && (!OWN || j + u > jmin))
-        atomicAdd(lds_ptr(hx + ex[u].y - (ex[u].x << 7)), 1u);
+    }
+    if (XT && anyx) {
+#pragma unroll
+      for (int u = 0; u < 4; u++)
+        if (s[u] < topx && (!OWN || j + u > jmin))
+          atomicAdd(lds_ptr(hx + ex[u].y - (ex[u].x << 7)), 1u);
     }
   });
   if (KX > 0) {
