@@ -705,7 +705,7 @@ static int num_cus() {
 // CP_WP_COPIES (a power of two up to the same most) overrides the choice.
 static int wp_copies(int mode, int prec, int weighted, int n32, int n64, int nb, int npi,
                      int nx = 0, int nbx = 0, bool shared = false) {
-  if (mode != WP && mode != WPXI) return 1;
+  if (mode == XI) return 1;
   if (const char *e = getenv("CP_WP_COPIES")) {
     const int c = atoi(e);
     if (c >= 1 && c <= (shared ? 32 : 8) && !(c & (c - 1))) return c;
@@ -770,9 +770,10 @@ static int launch_pairs_t(hipStream_t st, const PairParams &P, size_t lds, int n
 
 static int launch_pairs(hipStream_t st, int mode, int prec, int w, const PairParams &P,
                         size_t lds, int nwaves, int *grid) {
-  if (mode == WPXI) {
+  if (fused_mode(mode)) {
     if (prec != F32R || w) return fail(CP_ERR_INTERNAL, "fused w_p + xi is binary32, unweighted");
-    return launch_pairs_t<WPXI, F32R, 0>(st, P, lds, nwaves, grid);
+    return mode == WPXI ? launch_pairs_t<WPXI, F32R, 0>(st, P, lds, nwaves, grid)
+                        : launch_pairs_t<WPXR, F32R, 0>(st, P, lds, nwaves, grid);
   }
   if (mode == XI) {
     if (prec == F32R)
@@ -1765,6 +1766,7 @@ struct cp_plan {
   // xi and w_p in one launch (binary32): the w_p batch's build and pair
   // launch serve both statistics; xi keeps only its histogram
   bool fused = false;
+  cp::Mode fused_as = cp::WPXI;  // WPXI or WPXR
   cp::Binning xbin;              // xi decision table of the fused estimate
   uint2 *d_tabx = nullptr;
   double *d_Ex = nullptr;
@@ -1879,6 +1881,18 @@ static void batch_carve(Carver &cv, cp_plan &pl, Batch &b) {
   b.d_err = cv.take<int>(1);
 }
 
+// Which of the two fused kernels: edge chains over groups of four records win
+// where a box of R_max / 2 by R_max / 2 by pi_max / 2 holds more than some 28 points
+// of the largest catalogue, a lookup per pair below (sparse units have few
+// records, and coarse grids, best there, units over many slots).  Tuned plans of
+// two catalogues, chains / lookups in ms, at so many points: R_max 25, pi_max 40,
+// 14 bins 1.30 / 1.16 at 17, 2.39 / 2.18 at 25, 3.06 / 3.22 at 34, 5.51 / 6.01 at 51;
+// R_max 10, pi_max 10 0.28 / 0.25 at 8, 1.07 / 1.16 at 31; R_max 4 4.17 / 3.66 at 13;
+// R_max 60 0.387 / 0.404 at 22, 0.81 / 0.92 at 44.
+static bool plan_by_record(int64_t n, double box, double EB, double pimax) {
+  return (double)n / box / box / box * 0.125 * EB * pimax < 28.0;
+}
+
 static int batch_upload(cp_plan &pl, Batch &b) {
   if (!b.on) return CP_OK;
   const int nm = pl.nmock;
@@ -1891,7 +1905,8 @@ static int batch_upload(cp_plan &pl, Batch &b) {
   HIPCHK(hipMemcpy(b.d_col_prefix, b.col_prefix.data(), 8 * (nm + 1), hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(b.d_maxspan, b.maxspan.data(), 4 * nm, hipMemcpyHostToDevice));
   if (!b.B.t32.e.empty())
-    HIPCHK(hipMemcpy(b.d_t32, (few_edge_tables(b.mode, b.prec, 0) ? b.B.few : b.B.t32).e.data(),
+    HIPCHK(hipMemcpy(b.d_t32, (few_edge_tables(pl.fused ? pl.fused_as : b.mode, b.prec, 0)
+                                   ? b.B.few : b.B.t32).e.data(),
                      8 * b.B.t32.e.size(), hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(b.d_t64, b.B.t64.e.data(), 8 * b.B.t64.e.size(), hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(b.d_E, b.B.E.data(), 8 * (b.nb + 1), hipMemcpyHostToDevice));
@@ -2008,7 +2023,7 @@ static int batch_enqueue(cp_plan &pl, Batch &b, hipStream_t st) {
                      b.d_segs + nm, 1, b.S.tsum);
   hipLaunchKernelGGL(k_tiles, dim3(tb), dim3(256), 0, st, b.d_geom, nm, b.S.cstart, b.d_maxspan,
                      b.d_col_prefix, b.S.colcnt, b.S.coloff, b.S.tiles, 1);
-  return launch_pairs(st, (pl.fused && &b == &pl.wp) ? WPXI : b.mode, b.prec, 0, b.P, b.lds,
+  return launch_pairs(st, (pl.fused && &b == &pl.wp) ? pl.fused_as : b.mode, b.prec, 0, b.P, b.lds,
                       b.nwaves, &b.grid);
 }
 
@@ -2186,6 +2201,7 @@ static int plan_create(const cp_points *mocks, int nmocks, const double *xi_edge
     if (want_fused && pl->xi.prec == F32R && pl->wp.prec == F32R &&
         make_binning_wpxi(xi_edges, xi_nedges, pl->wp.B, pl->xbin)) {
       Batch &b = pl->wp;
+      pl->fused_as = plan_by_record(pl->maxn, o->boxsize, b.B.E[b.nb], b.pimax) ? WPXR : WPXI;
       const int n32 = (int)b.B.t32.e.size(), n64 = (int)b.B.t64.e.size();
       const int nx = (int)pl->xbin.t32.e.size(), nbx = xi_nedges - 1;
       b.wpc = wp_copies(WPXI, F32R, 0, n32, n64, b.nb, b.npi, nx, nbx);
@@ -2222,7 +2238,8 @@ static int plan_create(const cp_points *mocks, int nmocks, const double *xi_edge
     }
     if (pl->fused) {
       const Binning &X = pl->xbin;
-      if (hipMemcpy(pl->d_tabx, X.few.e.data(), 8 * X.few.e.size(), hipMemcpyHostToDevice) !=
+      const Table &tx = few_edge_tables(pl->fused_as, F32R, 0) ? X.few : X.t32;
+      if (hipMemcpy(pl->d_tabx, tx.e.data(), 8 * tx.e.size(), hipMemcpyHostToDevice) !=
               hipSuccess ||
           hipMemcpy(pl->d_Ex, X.E.data(), 8 * (size_t)xi_nedges, hipMemcpyHostToDevice) !=
               hipSuccess) {

@@ -110,8 +110,10 @@ std::string tune_cache_file();
 // WPXI: w_p and xi of the same catalogues in one pass over the w_p search
 // (binary32 mode; every xi pair lies inside the w_p cylinder when the xi
 // R_max is at most both r_p,max and pi_max).  Where the kernel tests
-// MODE == XI, WPXI takes the w_p side.
-enum Mode { XI = 0, WP = 1, WPXI = 2 };
+// MODE == XI, WPXI takes the w_p side.  WPXR: the same, record by record through
+// decision tables (plan_by_record).
+enum Mode { XI = 0, WP = 1, WPXI = 2, WPXR = 3 };
+__host__ __device__ constexpr bool fused_mode(int mode) { return mode == WPXI || mode == WPXR; }
 enum Prec { F64 = 0, F32R = 1 };
 
 // Geometry of one catalogue's cell grid.  Cells are ordered x-major, z
@@ -213,7 +215,7 @@ struct PairParams {
                              // tile count (written by the pair kernel), items by position,
                              // queue heads
   int hist_stride;           // nb * npi
-  // xi of a WPXI launch: few-edge table of s~ = fl32(pi~^2 + rp~^2) (bands
+  // xi of a WPXI (WPXR) launch: few-edge (decision) table of s~ = fl32(pi~^2 + rp~^2) (bands
   // of its own error bound), squared edges, histogram
   const uint2 *tabx;
   int tabx_lo, tabx_hi, tabx_shift;
@@ -260,11 +262,14 @@ struct LdsLayout {
 __host__ __device__ constexpr bool xi_f32_weighted(int mode, int prec, int weighted) {
   return mode == XI && prec == F32R && weighted;
 }
-// Kernels whose binary32 tables are few-edge tables (pair_kernels.hip,
-// wp_record) and which run no binary64 loop, hence hold no binary64 table: a
-// grid with a wrapped axis runs binary64 kernels.
-__host__ __device__ constexpr bool few_edge_tables(int mode, int prec, int weighted) {
+// Kernels which run no binary64 loop, hence hold no binary64 table: a grid with a
+// wrapped axis runs binary64 kernels; and of these the ones whose binary32
+// tables are few-edge tables (pair_kernels.hip, wp_record).
+__host__ __device__ constexpr bool no_f64_loops(int prec, int weighted) {
   return prec == F32R && !weighted;
+}
+__host__ __device__ constexpr bool few_edge_tables(int mode, int prec, int weighted) {
+  return no_f64_loops(prec, weighted) && mode != WPXR;
 }
 // Columns of a wave's xi counters, one per pair of lanes (lane mod 32: LDS takes
 // a wave's atomics 32 lanes at a time, so the pair never meets); one per lane
@@ -295,7 +300,7 @@ constexpr int kListCap = 64 + 4 * 64;
 
 // wpc: copies of the w_p histogram (and weight sums) per wave, or per workgroup
 // when its waves share one, interleaved counter by counter; lane l adds to copy l mod wpc.  nx, nbx: the xi table
-// entries and bins of a WPXI launch (xi rows, one per lane pair, follow the
+// entries and bins of a fused launch (xi rows, one per lane pair, follow the
 // w_p histogram).
 __host__ __device__ inline LdsLayout lds_layout(int mode, int prec, int weighted, int n32, int n64,
                                                int nb, int npi, int wpc = 1, int nx = 0,
@@ -304,7 +309,7 @@ __host__ __device__ inline LdsLayout lds_layout(int mode, int prec, int weighted
   size_t off = 0;
   L.tab32 = off;
   if (xi_f32_weighted(mode, prec, weighted)) n32 = 0;
-  if (few_edge_tables(mode, prec, weighted)) n64 = 0;
+  if (no_f64_loops(prec, weighted)) n64 = 0;
   off += (size_t)(prec == F32R ? n32 : 0) * 8;
   L.tab64 = off;
   off += (size_t)n64 * 8;
@@ -312,7 +317,7 @@ __host__ __device__ inline LdsLayout lds_layout(int mode, int prec, int weighted
   off += (size_t)(nb + 1) * 8;
   L.tabx = off;
   L.Ex = off;
-  if (mode == WPXI) {
+  if (fused_mode(mode)) {
     off += (size_t)nx * 8;
     L.Ex = off;
     off += (size_t)(nbx + 1) * 8;
@@ -325,7 +330,7 @@ __host__ __device__ inline LdsLayout lds_layout(int mode, int prec, int weighted
   L.wave_w = weighted ? (mode == XI ? (size_t)NS * kWStripe : words) * 8 : 0;
   L.wave_list = L.wave_hist + 2 * L.wave_w;
   L.wave_histx = L.wave_list + (xi_f32_weighted(mode, prec, weighted) ? (size_t)kListCap * 4 : 0);
-  L.wave_bytes = L.wave_histx + (mode == WPXI ? (size_t)(nbx + 2) * 32 * 4 : 0);
+  L.wave_bytes = L.wave_histx + (fused_mode(mode) ? (size_t)(nbx + 2) * 32 * 4 : 0);
   return L;
 }
 

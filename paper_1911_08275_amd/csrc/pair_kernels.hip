@@ -224,7 +224,7 @@ __device__ inline uint32_t *lds_ptr(uint32_t a) { return (uint32_t *)(lds_u32 *)
 
 struct WaveArea {
   uint32_t *hist;
-  uint32_t *histx;  // WPXI: the xi counters, one row of slots per lane pair (lane mod 32)
+  uint32_t *histx;  // fused: the xi counters, one row of slots per lane pair (lane mod 32)
   double *hw;   // weight sums, interleaved: hw[2 i] = sum w, hw[2 i + 1] = sum w r
   uint32_t *list;   // weighted xi, binary32 mode: (tile lane, record) pairs to evaluate
 };
@@ -301,7 +301,7 @@ __device__ inline void flush_group(const PairParams &P, const LdsLayout &LY, uns
     if (W && a != 0.0) unsafeAtomicAdd(gw + t, a);
     if (W && b != 0.0) unsafeAtomicAdd(gr + t, b);
   }
-  if (MODE == WPXI) {
+  if (fused_mode(MODE)) {
     for (int t = threadIdx.x; t < P.nbx; t += blockDim.x) {
       unsigned long long v = 0;
 #pragma unroll 1
@@ -354,7 +354,7 @@ __device__ inline void flush_hist(const PairParams &P, WaveArea A, int mock, int
       if (W && a != 0.0) unsafeAtomicAdd(P.hw + (int64_t)mock * P.hist_stride + t, a);
       if (W && b != 0.0) unsafeAtomicAdd(P.hwr + (int64_t)mock * P.hist_stride + t, b);
     }
-    if (MODE == WPXI) flush_xi_rows(A.histx, P.histx + (int64_t)mock * P.histx_stride, P.nbx, lane);
+    if (fused_mode(MODE)) flush_xi_rows(A.histx, P.histx + (int64_t)mock * P.histx_stride, P.nbx, lane);
   }
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -839,9 +839,8 @@ __device__ inline void wp_record(const PairParams &P, WaveArea A, const LanePt &
 // A unit of under kFewRecs records: one by one through wp_record, each loaded
 // ahead, with nothing to set up and no group to fill up (bound by latency; units
 // of a few records are what sparse catalogues have).  Pair kernel of w_p of 5.5
-// 10^5 points with 4 in reach of each 2.35 ms in groups, 1.85 one by one; w_p and xi
-// of catalogues like it 8.9 and 6.3.  2, 4, 8 and 16 records as the limit: 1.88,
-// 1.83, 1.82 and 1.83.
+// 10^5 points with 4 in reach of each 2.35 ms in groups, 1.85 one by one.  2, 4, 8
+// and 16 records as the limit: 1.88, 1.83, 1.82 and 1.83.
 constexpr int kFewRecs = 8;
 template <bool XIDEC>
 __device__ inline void loop_wp_single(const PairParams &P, WaveArea A, const LanePt &L, int jmin,
@@ -1011,6 +1010,68 @@ __device__ inline void loop_wp_f32(const PairParams &P, WaveArea A, const LanePt
     for (int k = 1; k < KX; k++) atomicAdd(hr + (xlo + k) * 32, nx[k] - nx[k - 1]);
     if (xlo + KX <= P.nbx) atomicAdd(hr + (xlo + KX) * 32, all - nx[NX - 1]);
   }
+}
+
+// The same statistics record by record (WPXR): each pair that is in range looks
+// its r_p bin and, XIDEC, its xi bin up in the decision tables; the lanes out of
+// range are masked off, so a record with none in range costs its estimates alone.
+// No chain to set up, a third of the code: see plan_by_record for where it wins.
+template <bool XIDEC, bool OWN>
+__device__ inline void loop_wpxr_f32(const PairParams &P, WaveArea A, const LanePt &L, int lane,
+                                     float rx, float ry, float rz, float ra, const Unit &U,
+                                     const uint2 *tab32, const double *sE, const uint2 *tabx,
+                                     const double *sEx, uint32_t &nrechk) {
+  const int wpc = P.wpc, cpy = lane & (wpc - 1);
+  const int lo = in_vgpr(P.tab32_lo), sh = in_vgpr(P.tab_shift);
+  const uint2 *tb = tab32 - P.tab32_lo;
+  const float AB = in_vgpr(P.AB32), phi = in_vgpr(P.pi_hi32), inv = in_vgpr(P.inv_dpi32);
+  const float pd = in_vgpr(P.pi_delta), pd1 = in_vgpr(1.0f - P.pi_delta);
+  // counter of slot kup - 1 (below) or kup of a table entry at pi bin l:
+  // row kup, l << lsh from h0 or h1
+  const uint32_t row4 = (uint32_t)in_vgpr(P.npi * wpc * 4);
+  const uint32_t lsh = (uint32_t)in_vgpr(2 + __builtin_ctz((unsigned)wpc));
+  const uint32_t h1 = lds_addr(A.hist) + 4u * (uint32_t)cpy, h0 = h1 - row4;
+  const int lox = in_vgpr(P.tabx_lo), shx = in_vgpr(P.tabx_shift), nbx = P.nbx;
+  const uint2 *tbx = tabx - P.tabx_lo;
+  const float ABx = in_vgpr(P.AB32x);
+  const uint32_t x1 = lds_addr(A.histx) + 4u * (uint32_t)(lane & 31), x0 = x1 - 128u;
+  uint32_t n = 0;
+  stream_f32(U.strm, U.jb, U.je, [&](int j, float qx, float qy, float qz, float qw) {
+    const float v = __builtin_fmaf(ry, qy, __builtin_fmaf(rx, qx, ra)) + qw;
+    const float pz = fabsf(qz - rz);
+    const bool ok = OWN ? j > L.iloc : true;
+    if (ok && v < AB && pz < phi) {
+      const uint2 e = tb[max(__float_as_int(v) >> sh, lo)];
+      const float f = pz * inv, fr = __builtin_amdgcn_fractf(f);
+      const bool ch = v >= __uint_as_float(e.y);
+      if ((v >= __uint_as_float(e.x) && !ch) || fr < pd || fr > pd1) {
+        recheck_wp<true>(P, A, L, U, j, sE, cpy);
+        n++;
+      } else {
+        const uint32_t at = __umul24(e.y & 63u, row4) + (ch ? h1 : h0);
+        atomicAdd(lds_ptr(lshl_add((uint32_t)f, lsh, at)), 1u);
+      }
+    }
+    if (XIDEC) {
+      const float sx = __builtin_fmaf(pz, pz, v);
+      if (ok && sx < ABx) {
+        const uint2 e = tbx[max(__float_as_int(sx) >> shx, lox)];
+        const bool ch = sx >= __uint_as_float(e.y);
+        uint32_t at = lshl_add(e.y & 63u, 7u, ch ? x1 : x0);
+        if (sx >= __uint_as_float(e.x) && !ch) {
+          sdouble *DP = (sdouble *)U.pos;
+          const int wz[3] = {0, 0, 0};
+          double dx, dy, dz;
+          ref_sep<true, false>(L.x, L.y, L.z, DP[4 * j], DP[4 * j + 1], DP[4 * j + 2], U.S, wz,
+                               0.0, 0.0, dx, dy, dz);
+          at = x1 + 128u * (uint32_t)exact_slot_bisect(sEx, nbx, (dx * dx + dy * dy) + dz * dz);
+          n++;
+        }
+        atomicAdd(lds_ptr(at), 1u);
+      }
+    }
+  });
+  nrechk += n;
 }
 
 // wp, weighted: every in-range pair is evaluated in binary64 for its rp.
@@ -1474,8 +1535,8 @@ void k_pairs(PairParams P) {
   const int lane = threadIdx.x & 63;
   const int wid = threadIdx.x >> 6;
   const int n32 = (PREC == F32R && !xi_f32_weighted(MODE, PREC, W)) ? P.tab32_hi - P.tab32_lo + 1 : 0;
-  const int n64 = few_edge_tables(MODE, PREC, W) ? 0 : P.tab64_hi - P.tab64_lo + 1;
-  const int nx = MODE == WPXI ? P.tabx_hi - P.tabx_lo + 1 : 0;
+  const int n64 = no_f64_loops(PREC, W) ? 0 : P.tab64_hi - P.tab64_lo + 1;
+  const int nx = fused_mode(MODE) ? P.tabx_hi - P.tabx_lo + 1 : 0;
   const LdsLayout LY = lds_layout(MODE, PREC, W, n32, n64, P.nb, P.npi, P.wpc, nx, P.nbx);
   uint2 *tab32 = (uint2 *)(smem + LY.tab32);
   uint2 *tab64 = (uint2 *)(smem + LY.tab64);
@@ -1491,10 +1552,11 @@ void k_pairs(PairParams P) {
   for (int t = threadIdx.x; t <= P.nb; t += blockDim.x) sE[t] = P.E[t];
   uint2 *tabx = (uint2 *)(smem + LY.tabx);
   double *sEx = (double *)(smem + LY.Ex);
-  if (MODE == WPXI) {
+  if (fused_mode(MODE)) {
     for (int t = threadIdx.x; t < nx; t += blockDim.x) {
-      const uint2 e = P.tabx[t];
-      tabx[t] = make_uint2(e.x, (e.y & 0x80000000u) | (e.y & 63u) << 7);
+      uint2 e = P.tabx[t];
+      if (FEW) e.y = (e.y & 0x80000000u) | (e.y & 63u) << 7;
+      tabx[t] = e;
     }
     for (int t = threadIdx.x; t <= P.nbx; t += blockDim.x) sEx[t] = P.Ex[t];
   }
@@ -1506,7 +1568,7 @@ void k_pairs(PairParams P) {
   A.hw = (double *)(wb + LY.wave_hist);
   A.list = (uint32_t *)(wb + LY.wave_list);
   A.histx = (uint32_t *)(wb + LY.wave_histx);
-  if (MODE == WPXI) {
+  if (fused_mode(MODE)) {
     for (int t = lane; t < (P.nbx + 2) * 32; t += 64) A.histx[t] = 0u;
   }
   const int NS = P.nslots;
@@ -1660,9 +1722,9 @@ void k_pairs(PairParams P) {
                 const double slo = rp + m[2] * m[2], shi = rpM + M[2] * M[2];
                 slots = exact_slot(sE, P.nb, slo) | (exact_slot(sE, P.nb, shi) << 8);
               } else if (PREC == F32R && !W) {
-                // r_p slots, and (WPXI) xi slots in the next two bytes
+                // r_p slots, and (fused) xi slots in the next two bytes
                 slots = exact_slot_top(sE, P.nb, rp) | (exact_slot_top(sE, P.nb, rpM) << 8);
-                if (MODE == WPXI)
+                if (fused_mode(MODE))
                   slots |= exact_slot_top(sEx, P.nbx, rp + m[2] * m[2]) << 16 |
                            exact_slot_top(sEx, P.nbx, rpM + M[2] * M[2]) << 24;
               }
@@ -1685,7 +1747,7 @@ void k_pairs(PairParams P) {
                   zwindow(P.pos2 + pbase2, zl, zh, rb, re);
                   if (re <= rb) ok = false;
                 }
-                mrg = PREC == F64 && MODE != WPXI ? 1 : 0;
+                mrg = PREC == F64 ? 1 : 0;
               }
             }
           }
@@ -1715,7 +1777,7 @@ void k_pairs(PairParams P) {
         // takes (own, or more than three slots); the run reaches from its first
         // cell's window to its last one's.
         int nrun = 1, last = src, slr = sl;
-        if (PREC == F64 && MODE != WPXI && (kc & 256)) {
+        if (PREC == F64 && (kc & 256)) {
           auto general = [&](int v, int p) {
             return ((p >> 30) & 1) || ((v >> 8) & 255) - (v & 255) > 2;
           };
@@ -1823,7 +1885,7 @@ void k_pairs(PairParams P) {
               else loop_xi_f32<false>(P, A, L, lane, rxf, ryf, rzf, ra, U, tab32, sE, nrechk);
             }
 #undef CP_XF
-          } else if (MODE == WPXI) {
+          } else if (fused_mode(MODE)) {
             const float ra = __builtin_fmaf(ryf, ryf, rxf * rxf);
             const int kw = U.slot_hi - U.slot_lo;
             const int xlo = (sl >> 16) & 255, kx = (int)(((unsigned)sl >> 24) - (unsigned)xlo);
@@ -1832,7 +1894,7 @@ void k_pairs(PairParams P) {
             // faster, and this kernel is already larger than the instruction
             // cache: 46.0 and 46.1 ms for 16 catalogues)
             const bool sure = !own && !P.noprune, none = sure && xlo > P.nbx;
-            const bool few = nj < kFewRecs;
+            const bool few = MODE == WPXI && nj < kFewRecs;
             const bool once = sure && !none && kx == 0 && !few;
             if (once && xlo >= 1 && valid) atomicAdd(&A.histx[xlo * 32 + (lane & 31)], (uint32_t)nj);
             const int kk = none || once ? 0 : kx;
@@ -1840,14 +1902,20 @@ void k_pairs(PairParams P) {
 #define CP_WX(K, KX, O) loop_wp_f32<K, KX, O>(P, A, L, lane, rxf, ryf, rzf, ra, U, xlo, tab32, sE, tabx, sEx, nrechk)
 #define CP_WXK(K) { if (kk == 0) CP_WX(K, 0, false); else if (kk == 1) CP_WX(K, 1, false); \
                     else CP_WX(K, 2, false); }
+#define CP_WR(X, O) loop_wpxr_f32<X, O>(P, A, L, lane, rxf, ryf, rzf, ra, U, tab32, sE, tabx, sEx, nrechk)
             if (valid) {
-              if (few) CP_FEW(true);
+              if (MODE == WPXR) {
+                if (own) CP_WR(true, true);
+                else if (kk == 0 && sure) CP_WR(false, false);
+                else CP_WR(true, false);
+              } else if (few) CP_FEW(true);
               else if (own) CP_WX(0, -1, true);
               else if (sure && kw <= 2 && U.slot_hi >= 1 && kk <= 2) {
                 if (kw <= 1) CP_WXK(1) else CP_WXK(2)
               } else if (kk == 0 && sure) CP_WX(0, 0, false);
               else CP_WX(0, -1, false);
             }
+#undef CP_WR
 #undef CP_WXK
 #undef CP_WX
           } else if (!W) {
@@ -1899,7 +1967,7 @@ void k_pairs(PairParams P) {
               else loop_xi_f64_two<false>(P, A, L, lane, U, sE);
             }
           }
-        } else if (!few_edge_tables(MODE, PREC, W)) {
+        } else if (!no_f64_loops(PREC, W)) {
 #define CP_F64(O, SH, WR) loop_f64<MODE, O, SH, WR, W>(P, A, L, lane, U, wrapax, box, half, tab64, sE)
           if (anywrap) {
             if (own) CP_F64(true, true, true); else CP_F64(false, true, true);
@@ -1952,5 +2020,6 @@ template __global__ void k_pairs<WP, F32R, 1>(PairParams);
 template __global__ void k_pairs<WP, F64, 0>(PairParams);
 template __global__ void k_pairs<WP, F64, 1>(PairParams);
 template __global__ void k_pairs<WPXI, F32R, 0>(PairParams);
+template __global__ void k_pairs<WPXR, F32R, 0>(PairParams);
 
 } // namespace cp

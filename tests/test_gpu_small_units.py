@@ -50,3 +50,31 @@ def test_units_around_the_limit(native, per, name, edges):
         plan.close()
         for m in range(2):
             assert (pw[m].reshape(wp.shape) == wp).all() and (px[m] == xi).all()
+
+
+@pytest.mark.parametrize("edges", [np.array([0.5, 6.0]), np.linspace(0.25, 6.0, 11),
+                                   np.array([0.5, 2.0, 2.0 + 1e-7, 3.0, 5.75, 6.0])])
+@pytest.mark.parametrize("refine", [(1, 1, 1), (3, 3, 2), (2, 2, 8)])
+@pytest.mark.parametrize("n", [4500, 7000])
+def test_fused_by_density(native, n, refine, edges):
+    """w_p and xi in one launch on either side of the density that picks its
+    kernel (6 100 points here): xi edges as the r_p edges, fewer and more."""
+    box, rng = 18.5, np.random.Generator(np.random.PCG64(n))
+    cats = []
+    for m in (n, 700, 5):
+        p = rng.uniform(0.0, box, (m, 3))
+        p[::2] = rng.integers(0, int(4 * box), p[::2].shape) * 0.25
+        cats.append(synth.Catalog(*(np.ascontiguousarray(p[:, a]) for a in range(3))))
+    devs = [native.to_device(c) for c in cats]
+    for xe in (edges, np.array([0.25, 0.5, 2.5]), np.linspace(0.5, 6.0, 23)):
+        print("fused", n, refine, len(edges), len(xe), flush=True)
+        plan = native.Plan(devs, xi_edges=xe, wp_edges=edges, pimax=6.0, npibins=6,
+                           precision="fp32", periodic=True, boxsize=box, refine=refine)
+        for _ in range(2):
+            plan.execute()
+            xi, wp = plan.results()
+            for m, c in enumerate(cats):
+                rw = oracle.wp(c, edges, 6.0, 6, periodic=True, box=box).npairs
+                assert (wp[m].reshape(rw.shape) == rw).all(), m
+                assert (xi[m] == oracle.xi(c, xe, periodic=True, box=box).npairs).all(), m
+        plan.close()
