@@ -91,16 +91,10 @@ __device__ inline int exact_slot(const double *E, int nb, double s) {
   return k + 1;
 }
 
-// The same scanned from the outermost edge inwards, where most bounds of
-// separations lie.
-__device__ inline int exact_slot_top(const double *E, int nb, double s) {
-  int k = nb + 1;
-  while (k > 0 && s < E[k - 1]) k--;
-  return k;
-}
-
 // The same by halving, at most six dependent reads: for the re-evaluations, whose
-// pairs may lie anywhere.
+// pairs may lie anywhere, and for the bounds of w_p units (scanned from the
+// outermost edge, pair kernel of w_p of 1.4 10^5 sparse points in 60 bins 0.48 ms,
+// halved 0.34; of w_p and xi 2.08 and 1.34).
 __device__ inline int exact_slot_bisect(const double *E, int nb, double s) {
   int lo = 0, hi = nb + 1;   // edges [0, lo) are at or below s, [hi, nb] above
   while (lo < hi) {
@@ -1723,10 +1717,10 @@ void k_pairs(PairParams P) {
                 slots = exact_slot(sE, P.nb, slo) | (exact_slot(sE, P.nb, shi) << 8);
               } else if (PREC == F32R && !W) {
                 // r_p slots, and (fused) xi slots in the next two bytes
-                slots = exact_slot_top(sE, P.nb, rp) | (exact_slot_top(sE, P.nb, rpM) << 8);
+                slots = exact_slot_bisect(sE, P.nb, rp) | (exact_slot_bisect(sE, P.nb, rpM) << 8);
                 if (fused_mode(MODE))
-                  slots |= exact_slot_top(sEx, P.nbx, rp + m[2] * m[2]) << 16 |
-                           exact_slot_top(sEx, P.nbx, rpM + M[2] * M[2]) << 24;
+                  slots |= exact_slot_bisect(sEx, P.nbx, rp + m[2] * m[2]) << 16 |
+                           exact_slot_bisect(sEx, P.nbx, rpM + M[2] * M[2]) << 24;
               }
               // z-window of the unit in the cell's own coordinates (Section
               // 2.2, late entry / early exit): a pair within reach has
