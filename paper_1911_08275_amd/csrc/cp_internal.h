@@ -286,7 +286,8 @@ constexpr int kXiCols = 32;
 // points 1.01 to 1.04).  The weighted w_p kernels hold fewer histogram copies in
 // the LDS of more workgroups: 250 000 binary64 points 0.44 / 0.63, 5 10^4 by
 // 4 10^5 binary32 points 0.43 / 0.47; unweighted binary64 w_p is as fast with
-// either, 10^6 points 2.05 / 2.05, 250 000 points 0.317 / 0.314.
+// either, 10^6 points 2.05 / 2.05, 250 000 points 0.317 / 0.314.  WPXR keeps five,
+// with which its loops were measured against the chains (plan_by_record).
 // Weighted xi with the binary32 filter holds a pair list per wave and fits
 // four workgroups per CU in LDS.
 __host__ __device__ constexpr int pair_waves(int mode, int prec, int weighted) {

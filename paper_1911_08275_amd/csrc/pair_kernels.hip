@@ -787,7 +787,8 @@ __device__ inline void recheck_wp(const PairParams &P, WaveArea A, const LanePt 
 // uncertain; a cell near none has t = -3e38.
 
 // One record in that way, pair by pair, for the few records that the loop
-// below finds to hold an uncertain pair: those are re-evaluated in binary64.
+// below finds to hold an uncertain pair (those are re-evaluated in binary64), and
+// for units of few records.
 template <bool XIDEC>
 __device__ inline void wp_record(const PairParams &P, WaveArea A, const LanePt &L, int jmin,
                                  int lane, float rx, float ry, float rz, float ra, const Unit &U,
@@ -870,7 +871,7 @@ __device__ inline void loop_wp_single(const PairParams &P, WaveArea A, const Lan
 // distance of a pi fraction from 1/2 tell with one branch whether any of their
 // pairs is uncertain, and then the four take wp_record.  Bound: VALU issue.
 // Against a decision-table lookup per pair with its compares: w_p of 10^6
-// points 1.88 to 1.63 ms a call, 16 catalogues' w_p and xi 51.0 to 46.1 ms (both
+// points 1.88 to 1.59 ms a call, 16 catalogues' w_p and xi 51.2 to 45.6 ms (both
 // with the record groups loaded ahead).
 // exec = valid lanes.
 template <int K, int KX, bool OWN>
